@@ -62,7 +62,7 @@ bool size_supported(int n) {
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Layout {
-    size_t T, T2, dfd, prow, pcf, pci, pupd, pres, pmace, scal, cnt, tvu, tvp, pl21;
+    size_t T, T2, dfd, prow, pcf, pci, pupd, pres, pmace, scal, cnt, tvp, pl21;
     size_t dfdb, pzi, pzf;  // 3D operator: box data [L][K][P], range-pass partial sums
     size_t total;
 };
@@ -244,8 +244,7 @@ void layout_scene(Scene& s) {
     w.pmace = take((size_t)std::max(clampk::mace_blocks(s.n()), clampk::row_blocks(s.tab)) * 2 * sizeof(double));
     w.scal = take(64 * sizeof(double));
     w.cnt = take(64 * sizeof(unsigned));
-    w.tvu = take(s.n() * sizeof(float));
-    w.tvp = take(3 * s.n() * sizeof(float));
+    w.tvp = take(6 * s.n() * sizeof(float));
     w.pl21 = take((size_t)s.sc.nz * clampk::l21_chunks(s.sc.nx, s.sc.ny) * sizeof(double));
     if (s.K > 0) {
         const size_t nz_blocks = (size_t)std::max(clampk::zpass_blocks(s.tab), clampk::gather_blocks(s.tab));
@@ -887,7 +886,7 @@ clamp_status clamp_prior_tv(const clamp_plan* plan, int32_t scene, float lam, in
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const hipError_t e = timed(plan, ST_PRIOR, stream, [&] {
         return clampk::launch_prior_tv(s.sc.nx, s.sc.ny, s.sc.nz, lam, iters, in, out, at<float>(workspace, s.ws.tvp),
-                                       at<float>(workspace, s.ws.tvu), stream);
+                                       stream);
     });
     return hip_check(e, "clamp_prior_tv launch");
 }

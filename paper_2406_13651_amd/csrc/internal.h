@@ -213,12 +213,12 @@ hipError_t mace_scratch(int device, double** out);
 
 // Comparison regularizers (regularizers.hip): the l_{2,1} proximal map
 // (part: nz * l21_chunks(nx, ny) doubles) and the TV proximal map by
-// Chambolle's iteration (p: 3 n floats, u: n floats of scratch).
+// Chambolle's iteration (p: 6 n floats of scratch).
 int l21_chunks(int nx, int ny);
 hipError_t launch_prior_l21(int nx, int ny, int nz, float tau, const float* in, float* out, double* part,
                             hipStream_t st);
 hipError_t launch_prior_tv(int nx, int ny, int nz, float lam, int iters, const float* in, float* out, float* p,
-                           float* u, hipStream_t st);
+                           hipStream_t st);
 
 hipError_t launch_gauss(int nx, int ny, int nz, const float* taps7, const float* in, float* out, hipStream_t st);
 
