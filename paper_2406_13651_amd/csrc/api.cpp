@@ -96,6 +96,7 @@ struct TimingRecord {
 
 struct clamp_plan {
     int device = 0;
+    int cus = 256;  // compute units of the device
     std::vector<Scene> scenes;
     size_t ws_bytes = 0;
     uint32_t timing = 0u;  // bit s: record events around stage s
@@ -236,12 +237,12 @@ void layout_scene(Scene& s) {
     w.T = take(band);
     w.T2 = take(band);
     w.dfd = take(L * s.sc.nz * (size_t)s.P * sizeof(float2));
-    w.prow = take(L * clampk::row_blocks(s.tab) * 3 * sizeof(double));
+    w.prow = take(L * std::max(clampk::row_blocks(s.tab), s.sc.nz) * 3 * sizeof(double));  // per row block or slice
     w.pcf = take(L * clampk::col_blocks(s.tab) * sizeof(double));
     w.pci = take(L * clampk::col_blocks(s.tab) * sizeof(double));
-    w.pupd = take(L * clampk::row_blocks(s.tab) * sizeof(double));
+    w.pupd = take(L * std::max(clampk::row_blocks(s.tab), clampk::mann_blocks(s.tab, 4)) * sizeof(double));
     w.pres = take(L * clampk::resid_blocks(s.tab) * sizeof(double));
-    w.pmace = take((size_t)std::max(clampk::mace_blocks(s.n()), clampk::row_blocks(s.tab)) * 2 * sizeof(double));
+    w.pmace = take((size_t)std::max(clampk::mace_blocks(s.n()), clampk::mann_blocks(s.tab, 4)) * 2 * sizeof(double));
     w.scal = take(64 * sizeof(double));
     w.cnt = take(64 * sizeof(unsigned));
     w.tvp = take(6 * s.n() * sizeof(float));
@@ -343,6 +344,14 @@ hipError_t timed(const clamp_plan* cplan, int stage, hipStream_t st, F&& launch)
     return e != hipSuccess ? e : es;
 }
 
+int device_cus() {
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+        cus = 256;
+    return cus;
+}
+
 ColArgs col_args(const Scene& s, int looks) {
     ColArgs a{};
     a.s = s.tab;
@@ -393,6 +402,7 @@ clamp_status clamp_plan_create(const clamp_scene* scenes, int32_t nscenes, clamp
     clamp_plan* plan = new (std::nothrow) clamp_plan();
     if (plan == nullptr) return fail(CLAMP_ENOMEM, "host allocation failed");
     plan->device = dev;
+    plan->cus = device_cus();
     plan->scenes.resize(nscenes);
     for (int i = 0; i < nscenes; ++i) {
         clamp_status st = build_scene(scenes[i], plan->scenes[i]);
@@ -686,8 +696,11 @@ RowArgs agent_row_args(const AgentRun& r, const float* w) {
     return ra;
 }
 
+// fused: the update is the pass with the Mann step, whose convergence error
+// (its partials in fused->part) goes to conv_err beside the diagnostics.
 template <typename Update>
-hipError_t agent_launches(const AgentRun& r, const RowArgs& ra, Update&& update) {
+hipError_t agent_launches(const AgentRun& r, const RowArgs& ra, const clampk::FuseArgs* fused, double* conv_err,
+                          Update&& update) {
     const Scene& s = r.s;
     const clamp_plan* plan = r.plan;
     void* workspace = r.workspace;
@@ -717,6 +730,35 @@ hipError_t agent_launches(const AgentRun& r, const RowArgs& ra, Update&& update)
         clampk::ZArgs za{s.tab, L, resid, dfd, pz_inv};
         e = timed(plan, ST_RANGE_INV, stream, [&] { return clampk::launch_zpass(+1, za, stream); });
     }
+    // partial-sum sets per look of the row side and of the column side (with
+    // the 3D operator the latter come from the range passes)
+    int nrow = clampk::row_blocks(s.tab), ncol = range ? clampk::zpass_blocks(s.tab) : clampk::col_blocks(s.tab);
+    if (clampk::slice_path(s.tab)) {
+        clampk::SliceArgs sa{};
+        sa.s = s.tab;
+        sa.looks = L;
+        sa.cmp_in = range ? dfd : resid;
+        sa.cmp_out = dfd;
+        sa.band_out = T;
+        sa.mu = ra.mu;
+        sa.r = ra.r;
+        sa.prow = prow;
+        sa.pcf = range ? nullptr : pcf;
+        sa.pci = range ? nullptr : pci;
+        sa.scale = ra.scale;
+        sa.scale_y = col_args(s, L).scale;
+        sa.inv_s2w = ra.inv_s2w;
+        sa.floor_w = ra.floor_w;
+        nrow = s.sc.nz;
+        if (!range) ncol = s.sc.nz;
+        // one launch, reported as the gradient stage; the column stages it
+        // contains are reported empty
+        const auto nothing = [] { return hipSuccess; };
+        if (e == hipSuccess) e = timed(plan, ST_COL_INV, stream, nothing);
+        if (e == hipSuccess)
+            e = timed(plan, ST_ROW_GRAD, stream, [&] { return clampk::launch_slice_grad(sa, stream); });
+        if (e == hipSuccess) e = timed(plan, ST_COL_FWD, stream, nothing);
+    } else {
     ColArgs ci = col_args(s, L);
     ci.cmp_in = range ? dfd : resid;
     ci.band_out = T;
@@ -737,6 +779,7 @@ hipError_t agent_launches(const AgentRun& r, const RowArgs& ra, Update&& update)
         cf.part = pcf;
         e = timed(plan, ST_COL_FWD, stream, [&] { return clampk::launch_col(clampk::COL_FWD_COMPACT, cf, stream); });
     }
+    }
     if (e == hipSuccess && range) {
         clampk::ZArgs za{s.tab, L, dfd, dfd_box, pz_fwd};
         e = timed(plan, ST_RANGE_FWD, stream, [&] { return clampk::launch_zpass(-1, za, stream); });
@@ -744,7 +787,7 @@ hipError_t agent_launches(const AgentRun& r, const RowArgs& ra, Update&& update)
     unsigned* counter = at<unsigned>(workspace, s.ws.cnt);
     if (e == hipSuccess)
         e = timed(plan, ST_GAMMA, stream, [&] {
-            return clampk::launch_gamma(s.tab, L, prow, pz_fwd, pz_inv, 1.0 / s2w, r.diag, r.fault, counter, stream);
+            return clampk::launch_gamma(nrow, ncol, L, prow, pz_fwd, pz_inv, 1.0 / s2w, r.diag, r.fault, counter, stream);
         });
     if (e == hipSuccess) {
         RowArgs u = ra;
@@ -757,7 +800,10 @@ hipError_t agent_launches(const AgentRun& r, const RowArgs& ra, Update&& update)
                   [&] { return clampk::launch_resid_update(s.tab, L, resid, dfd_box, r.diag, pres, stream); });
     if (e == hipSuccess)
         e = timed(plan, ST_DIAG, stream, [&] {
-            return clampk::launch_diag_after(s.tab, L, pupd, pres, s2w, r.state->ahy2, r.diag, counter, stream);
+            const int nmann = fused ? clampk::mann_blocks(s.tab, fused->split) : 0;
+            return clampk::launch_diag_after(fused ? nmann : clampk::row_blocks(s.tab), clampk::resid_blocks(s.tab), L,
+                                             pupd, pres, s2w, r.state->ahy2, r.diag, counter,
+                                             fused ? fused->part : nullptr, nmann, conv_err, stream);
         });
     return e;
 }
@@ -788,7 +834,7 @@ clamp_status clamp_fwd_agent(const clamp_plan* plan, int32_t scene, const clamp_
     const AgentRun run{plan, plan->scenes[scene], params, state, diag, fault, workspace,
                        static_cast<hipStream_t>(hip_stream)};
     const int mode = params->r_update == CLAMP_R_EXACT ? clampk::ROW_UPDATE_EXACT : clampk::ROW_UPDATE;
-    const hipError_t e = agent_launches(run, agent_row_args(run, w), [&](const RowArgs& u) {
+    const hipError_t e = agent_launches(run, agent_row_args(run, w), nullptr, nullptr, [&](const RowArgs& u) {
         return timed(plan, ST_ROW_UPDATE, run.stream, [&] { return clampk::launch_row(mode, u, run.stream); });
     });
     return hip_check(e, "clamp_fwd_agent launch");
@@ -815,15 +861,14 @@ clamp_status clamp_fwd_agent_mace(const clamp_plan* plan, int32_t scene, const c
     for (int j = 0; j < params->n_agents; ++j) f.ups[j] = params->upsilon[j];
     f.two_rho = 2.f * params->rho;
     f.n_agents = params->n_agents;
+    f.split = clampk::mann_split(s.tab, L, plan->cus);
     const int mode = params->r_update == CLAMP_R_EXACT ? clampk::ROW_UPDATE_EXACT : clampk::ROW_UPDATE;
-    hipError_t e = agent_launches(run, agent_row_args(run, w), [&](const RowArgs& u) {
+    hipError_t e = agent_launches(run, agent_row_args(run, w), &f, conv_err, [&](const RowArgs& u) {
         return timed(plan, ST_ROW_UPDATE_MANN, run.stream,
                      [&] { return clampk::launch_row_update_mann(mode, u, f, run.stream); });
     });
-    if (e == hipSuccess)
-        e = timed(plan, ST_MACE, run.stream, [&] {
-            return clampk::launch_mace_final(f.part, clampk::row_blocks(s.tab), conv_err, run.stream);
-        });
+    // the Mann step's final sums run in the diagnostics launch: an empty stage
+    if (e == hipSuccess) e = timed(plan, ST_MACE, run.stream, [] { return hipSuccess; });
     return hip_check(e, "clamp_fwd_agent_mace launch");
 }
 
@@ -1019,13 +1064,10 @@ namespace {
 
 constexpr int kBetaLen = 1 << 16;
 const int kLengths[clampk::kSizeClasses] = {512, 384, 256, 192, 128, 64, 32};
-
-int device_cus() {
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-        cus = 256;
-    return cus;
+int length_class(int n) {
+    for (int k = 0; k < clampk::kSizeClasses; ++k)
+        if (kLengths[k] == n) return k;
+    return 0;  // plan creation admits the supported lengths only
 }
 
 }  // namespace
@@ -1086,7 +1128,7 @@ hipError_t batch_run(clamp_batch* b, hipStream_t st) {
     const int plain[] = {BS_COL_INV, BS_ROW_GRAD, BS_COL_FWD, BS_GAMMA, BS_ROW_UPDATE, BS_RESID, BS_DIAG, BS_PRIOR};
     const int plain_t[] = {ST_COL_INV, ST_ROW_GRAD, ST_COL_FWD, ST_GAMMA, ST_ROW_UPDATE, ST_RESID, ST_DIAG, ST_PRIOR};
     const int fused[] = {BS_PRIOR, BS_COL_INV, BS_ROW_GRAD, BS_COL_FWD, BS_GAMMA, BS_ROW_UPDATE_MANN, BS_RESID,
-                         BS_DIAG};
+                         BS_FINISH};
     const int fused_t[] = {ST_PRIOR, ST_COL_INV, ST_ROW_GRAD, ST_COL_FWD, ST_GAMMA, ST_ROW_UPDATE_MANN, ST_RESID,
                            ST_DIAG};
     const int* stages = b->fused ? fused : plain;
@@ -1095,8 +1137,10 @@ hipError_t batch_run(clamp_batch* b, hipStream_t st) {
         const hipError_t e = timed(p, timing_stage[i], st, [&] { return batch_stage(stages[i], b->launch, st); });
         if (e != hipSuccess) return e;
     }
+    // the fused form's last launch holds the convergence errors and the counter
+    if (b->fused) return timed(p, ST_MACE, st, [] { return hipSuccess; });
     hipError_t e = timed(p, ST_MACE, st, [&] {
-        hipError_t x = b->fused ? hipSuccess : batch_stage(BS_MACE, b->launch, st);
+        hipError_t x = batch_stage(BS_MACE, b->launch, st);
         if (x == hipSuccess) x = batch_stage(BS_MACE_FINAL, b->launch, st);
         return x;
     });
@@ -1135,10 +1179,16 @@ clamp_status clamp_batch_create(const clamp_plan* plan, const clamp_batch_scene*
     if (n_fused != 0 && n_fused != ns)
         return fail(CLAMP_EINVAL, "either every scene of a batch has an xbar (the fused Mann step) or none has");
     const bool fused = n_fused == ns && ns > 0;
+    // the fused update pass of one row length is one launch over its scenes:
+    // four waves share a row group's looks (mann_split) where that launch
+    // still fits on the chip at once, else each wave walks every look
+    long blocks4[kSizeClasses] = {};
+    for (const Scene& s : plan->scenes) blocks4[length_class(s.sc.nx)] += mann_blocks(s.tab, 4);
     size_t ws_off = 0;
     for (int i = 0; i < ns; ++i) {
         const Scene& s = plan->scenes[i];
         const clamp_batch_scene& bs = scenes[i];
+        const int split = blocks4[length_class(s.sc.nx)] <= 3 * plan->cus ? 4 : 1;
         if ((st = check_params(s, &bs.params, true)) != CLAMP_OK) return fail(st, "scene %d: %s", i, g_err.c_str());
         if (bs.params.n_agents > 40) return fail(CLAMP_EUNSUPPORTED, "scene %d: a batch holds at most 40 agents", i);
         if (bs.params.r_update != CLAMP_R_QUADRATIC)
@@ -1190,7 +1240,7 @@ clamp_status clamp_batch_create(const clamp_plan* plan, const clamp_batch_scene*
                            at<double>(w0, s.ws.pci), 1.0 / s2w, bs.diag, fault, at<unsigned>(w0, s.ws.cnt)};
         sb.res = ResidArgs{(size_t)s.sc.nz * s.P, resid_chunks(s.tab), static_cast<float2*>(bs.state.resid),
                            at<float2>(w0, s.ws.dfd), bs.diag, at<double>(w0, s.ws.pres)};
-        sb.dia = DiagArgs{row_blocks(s.tab), resid_chunks(s.tab), L, at<double>(w0, s.ws.pupd),
+        sb.dia = DiagArgs{fused ? mann_blocks(s.tab, split) : row_blocks(s.tab), resid_chunks(s.tab), L, at<double>(w0, s.ws.pupd),
                           at<double>(w0, s.ws.pres), s2w, bs.state.ahy2, bs.diag, at<unsigned>(w0, s.ws.cnt)};
         MaceArgs m{};
         m.n = n;
@@ -1202,7 +1252,7 @@ clamp_status clamp_batch_create(const clamp_plan* plan, const clamp_batch_scene*
         m.wbar = bs.wbar;
         m.part = at<double>(w0, s.ws.pmace);
         sb.mace = m;
-        sb.mace_chunks = fused ? row_blocks(s.tab) : mace_blocks(n);
+        sb.mace_chunks = fused ? mann_blocks(s.tab, split) : mace_blocks(n);
         if (fused) {
             FuseArgs f{};
             f.u = bs.w;
@@ -1214,6 +1264,7 @@ clamp_status clamp_batch_create(const clamp_plan* plan, const clamp_batch_scene*
             for (int j = 0; j < m.n_agents; ++j) f.ups[j] = m.ups[j];
             f.two_rho = m.two_rho;
             f.n_agents = m.n_agents;
+            f.split = split;
             sb.fuse = f;
         }
         sb.with_prior = with_prior ? 1 : 0;
@@ -1235,15 +1286,11 @@ clamp_status clamp_batch_create(const clamp_plan* plan, const clamp_batch_scene*
         }
         sb.prior = pr;
         // work items
-        int li = 0, ci = 0;
-        for (int k = 0; k < kSizeClasses; ++k) {
-            if (kLengths[k] == s.sc.nx) li = k;
-            if (kLengths[k] == s.sc.ny) ci = k;
-        }
+        const int li = length_class(s.sc.nx), ci = length_class(s.sc.ny);
         for (int l = 0; l < L; ++l)
             for (int g = 0; g < row_blocks(s.tab); ++g) rows_by_len[li].push_back(BatchItem{i, l, g, 0});
         if (fused)
-            for (int g = 0; g < row_blocks(s.tab); ++g) rowg_by_len[li].push_back(BatchItem{i, 0, g, 0});
+            for (int g = 0; g < sb.mace_chunks; ++g) rowg_by_len[li].push_back(BatchItem{i, 0, g, 0});
         for (int it = 0; it < L * s.sc.nz * s.tiles; ++it) cols_by_len[ci].push_back(BatchItem{i, it, 0, 0});
         for (int l = 0; l < L; ++l) {
             q[Q_LOOK].push_back(BatchItem{i, l, 0, 0});
@@ -1274,6 +1321,7 @@ clamp_status clamp_batch_create(const clamp_plan* plan, const clamp_batch_scene*
             if (by[k].empty()) continue;
             const int g = L.nseg[side]++;
             L.seg_len[side][g] = kLengths[k];
+            if (side == 2) L.mann_split[g] = blocks4[k] <= 3 * plan->cus ? 4 : 1;
             L.seg_off[side][g] = (int)dst.size();
             L.seg_count[side][g] = (int)by[k].size();
             dst.insert(dst.end(), by[k].begin(), by[k].end());

@@ -50,11 +50,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(!PERSIST
     }
 }
 
-// The update pass with the Mann step fused in, one block per row-group item
-// (scene, row group) of the segment starting at `off`, walking every look of
-// the scene (row_update_mann); three waves per SIMD, as the single-scene
+// The update pass with the Mann step fused in, one block per item (scene,
+// block of the scene) of the segment starting at `off` (row_update_mann); three waves per SIMD, as the single-scene
 // kernel.
-template <int NX>
+template <int NX, int SPLIT>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) void kb_row_mann(BatchLaunch b,
                                                                                               int off) {
     __shared__ float2 tw[NX];
@@ -69,7 +68,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
     const BatchItem w = const_ref(b.queue[Q_ROWG] + off + blockIdx.x);
     const auto& a = const_ref(&b.scenes[w.scene].update);
     const auto& f = const_ref(&b.scenes[w.scene].fuse);
-    row_update_mann<NX, ROW_UPDATE>(a, f, w.b, row_blocks(a.s), L, bv, ups, keep);
+    row_update_mann<NX, ROW_UPDATE>(a, f, SPLIT, w.b, mann_blocks(a.s, SPLIT), L, bv, ups, keep);
 }
 
 // Column pass over the segment [off, off + count) of the column queue, whose
@@ -171,12 +170,23 @@ __global__ __launch_bounds__(kBlock) void kb_mace_final(BatchLaunch b) {
     const BatchItem* q = b.queue[Q_SCENE];
     for (int it = blockIdx.x; it < b.count[Q_SCENE]; it += gridDim.x) {
         const SceneBatch& sb = b.scenes[q[it].scene];
-        double v[2] = {0.0, 0.0};
-        strided_sums<2>(sb.mace.part, sb.mace_chunks, 2, v);
-        __shared__ double tot[2];
-        block_sum_store<2>(v, tot);
-        if (threadIdx.x == 0) sb.conv[0] = tot[1] > 0.0 ? sqrt(tot[0] / tot[1]) : 0.0;
+        mace_final_item(sb.mace.part, sb.mace_chunks, sb.conv);
     }
+}
+
+// The end of a fused step in one launch: the diagnostics of every look, the
+// convergence error of every scene, and (block 0) the iteration counter,
+// which the step's kernels before this one have read.
+__global__ __launch_bounds__(kBlock) void kb_finish(BatchLaunch b) {
+    const int nl = b.count[Q_LOOK], it = blockIdx.x;
+    if (it < nl) {
+        const BatchItem w = b.queue[Q_LOOK][it];
+        diag_after_item(w.a, load_uniform(&b.scenes[w.scene].dia));
+    } else {
+        const SceneBatch& sb = b.scenes[b.queue[Q_SCENE][it - nl].scene];
+        mace_final_item(sb.mace.part, sb.mace_chunks, sb.conv);
+    }
+    if (it == 0 && threadIdx.x == 0) b.iter[0] += 1;
 }
 
 __global__ void kb_set_iter(int* iter, int value, int add) {
@@ -226,7 +236,10 @@ static void launch_rowg_segments(const BatchLaunch& b, hipStream_t st) {
         switch (b.seg_len[2][g]) {
 #define CASE(N)                                                                            \
     case N:                                                                                \
-        hipLaunchKernelGGL((kb_row_mann<N>), dim3(cnt), dim3(kBlock), 0, st, b, off);      \
+        if (b.mann_split[g] == 1)                                                          \
+            hipLaunchKernelGGL((kb_row_mann<N, 1>), dim3(cnt), dim3(kBlock), 0, st, b, off); \
+        else                                                                               \
+            hipLaunchKernelGGL((kb_row_mann<N, 4>), dim3(cnt), dim3(kBlock), 0, st, b, off); \
         break;
             CLAMP_SIZES(CASE)
 #undef CASE
@@ -273,6 +286,9 @@ hipError_t batch_stage(int stage, const BatchLaunch& b, hipStream_t st) {
         case BS_ROW_UPDATE_MANN: launch_rowg_segments(b, st); break;
         case BS_MACE: go(Q_VOX, kb_mace); break;
         case BS_MACE_FINAL: go(Q_SCENE, kb_mace_final); break;
+        case BS_FINISH:
+            hipLaunchKernelGGL(kb_finish, dim3(b.count[Q_LOOK] + b.count[Q_SCENE]), dim3(kBlock), 0, st, b);
+            break;
         case BS_NEXT_ITER: hipLaunchKernelGGL(kb_set_iter, dim3(1), dim3(64), 0, st, b.iter, 1, 1); break;
         default: return hipErrorInvalidValue;
     }

@@ -209,9 +209,8 @@ __host__ __device__ constexpr bool fft_regs_ok() {
     return true;
 }
 
-template <int N, int T, int S, int PADSH, int STAGE, int NS, bool IN_REGS, bool OUT_REGS, bool WAVE>
-__device__ __forceinline__ void fft_regs_stages(float2 (&h)[N / T], float2* buf, int stride, int t,
-                                                const float2* tw) {
+template <int N, int T, int S, int STAGE, int NS, bool IN_REGS, bool OUT_REGS, bool WAVE, class Pos>
+__device__ __forceinline__ void fft_regs_stages(float2 (&h)[N / T], float2* buf, Pos pos, int t, const float2* tw) {
     constexpr int NST = num_stages(N);
     if constexpr (STAGE < NST) {
         constexpr int R = radix_at(N, STAGE);
@@ -230,7 +229,7 @@ __device__ __forceinline__ void fft_regs_stages(float2 (&h)[N / T], float2* buf,
 #pragma unroll
             for (int p = 0; p < PER; ++p)
 #pragma unroll
-                for (int r = 0; r < R; ++r) v[p][r] = buf[lds_pos<PADSH>(t + p * T + r * NB) * stride];
+                for (int r = 0; r < R; ++r) v[p][r] = buf[pos(t + p * T + r * NB)];
             group_sync<WAVE>();
         }
 #pragma unroll
@@ -253,24 +252,31 @@ __device__ __forceinline__ void fft_regs_stages(float2 (&h)[N / T], float2* buf,
             } else {
                 const int base = (j / NS) * NS * R + k;
 #pragma unroll
-                for (int r = 0; r < R; ++r) buf[lds_pos<PADSH>(base + r * NS) * stride] = v[p][r];
+                for (int r = 0; r < R; ++r) buf[pos(base + r * NS)] = v[p][r];
             }
         }
         if constexpr (!LAST_IN_REGS) group_sync<WAVE>();
-        fft_regs_stages<N, T, S, PADSH, STAGE + 1, NS * R, IN_REGS, OUT_REGS, WAVE>(h, buf, stride, t, tw);
+        fft_regs_stages<N, T, S, STAGE + 1, NS * R, IN_REGS, OUT_REGS, WAVE>(h, buf, pos, t, tw);
     }
 }
 
 // Unnormalised length-N DFT (see fft_regs_ok) of the group's vector, held in
-// h (IN_REGS) or in buf[lds_pos(i) * stride]; the result goes to h (OUT_REGS)
-// or to buf in natural order, visible to the group.  Starts with a group
-// synchronisation, so earlier reads and writes of buf by the group are done.
-template <int N, int T, int S, int PADSH, bool IN_REGS, bool OUT_REGS, bool WAVE>
-__device__ __forceinline__ void fft_regs(float2 (&h)[N / T], float2* buf, int stride, int t, const float2* tw) {
+// h (IN_REGS) or in buf[pos(i)]; the result goes to h (OUT_REGS) or to buf in
+// natural order, visible to the group.  Starts with a group synchronisation,
+// so earlier reads and writes of buf by the group are done.
+template <int N, int T, int S, bool IN_REGS, bool OUT_REGS, bool WAVE, class Pos>
+__device__ __forceinline__ void fft_regs_at(float2 (&h)[N / T], float2* buf, Pos pos, int t, const float2* tw) {
     static_assert(fft_len_ok(N) && fft_regs_ok<N, T>(), "length and group size outside the register form");
     static_assert(!WAVE || (T <= 64 && 64 % T == 0), "a wave-local transform must lie inside one wave");
     group_sync<WAVE>();
-    fft_regs_stages<N, T, S, PADSH, 0, 1, IN_REGS, OUT_REGS, WAVE>(h, buf, stride, t, tw);
+    fft_regs_stages<N, T, S, 0, 1, IN_REGS, OUT_REGS, WAVE>(h, buf, pos, t, tw);
+}
+
+// The same with element i at buf[lds_pos(i) * stride].
+template <int N, int T, int S, int PADSH, bool IN_REGS, bool OUT_REGS, bool WAVE>
+__device__ __forceinline__ void fft_regs(float2 (&h)[N / T], float2* buf, int stride, int t, const float2* tw) {
+    fft_regs_at<N, T, S, IN_REGS, OUT_REGS, WAVE>(
+        h, buf, [stride](int i) { return lds_pos<PADSH>(i) * stride; }, t, tw);
 }
 
 }  // namespace clampk

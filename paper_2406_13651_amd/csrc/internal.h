@@ -93,6 +93,15 @@ __host__ __device__ inline int row_blocks(const SceneTables& s) {
     const int rpb = rows_per_block(s.nx);
     return (s.nz * s.ny + rpb - 1) / rpb;
 }
+// Row groups of the fused update pass (the rows of one wave), and its blocks
+// when `split` of a block's four waves share a group.
+__host__ __device__ inline int row_groups(const SceneTables& s) {
+    const int rpw = 64 / row_threads(s.nx);
+    return (s.nz * s.ny + rpw - 1) / rpw;
+}
+__host__ __device__ inline int mann_blocks(const SceneTables& s, int split) {
+    return (row_groups(s) * split + 3) / 4;
+}
 __host__ __device__ inline int col_blocks(const SceneTables& s) { return s.nz * s.tiles; }
 // Launches of the residual update and the Mann step take one element (pair)
 // per thread: many short blocks stream HBM faster on this chip than a capped
@@ -145,6 +154,26 @@ struct RowArgs {
     float k_dn;                // beta (1 + beta)        (xi = r'/beta)
 };
 
+// Inverse column, gradient row and forward column passes of whole slices in
+// one launch (slice_grad_item), for slices whose band fits in LDS.
+struct SliceArgs {
+    SceneTables s;
+    int looks;
+    const float2* cmp_in;      // residual, compact [looks][nz][P]
+    float2* cmp_out;           // A d, compact
+    float2* band_out;          // band rows for the update pass
+    const float2* mu;          // [looks][n]
+    const float* r;            // [looks][n] anchors
+    double* prow;              // 3 per slice
+    double* pcf;               // 1 per slice, or NULL
+    double* pci;               // 1 per slice, or NULL
+    float scale;               // 1/sqrt(nx)
+    float scale_y;             // 1/sqrt(ny)
+    float inv_s2w, floor_w;    // as in RowArgs
+};
+bool slice_path(const SceneTables& s);  // whether launch_slice_grad takes this scene
+hipError_t launch_slice_grad(const SliceArgs& a, hipStream_t st);
+
 // The Mann step fused into the update pass (one block walks every look of
 // its rows).  The forward agents' Mann state is kept as u_l = w_l - 2 rho
 // xbar with xbar the reflected average x_bar of the previous step, so that
@@ -157,29 +186,33 @@ struct FuseArgs {
     const float* rprior;  // [n] the prior agent's output H(w) (NULL without a prior)
     float* xbar;          // [n] in: x_bar of the previous step, out: this step's
     float* wbar;          // [n] out: sum_j upsilon_j w_j after the step
-    double* part;         // [row_blocks][2] partial sums of the convergence error
+    double* part;         // [mann_blocks][2] partial sums of the convergence error
     float ups[64];
     float two_rho;
     int n_agents;
+    int split;            // waves that share a row group's looks: 1, 2 or 4 (mann_split)
 };
+int mann_split(const SceneTables& s, int looks, int cus);
 hipError_t launch_col(int mode, const ColArgs& a, hipStream_t st);
 hipError_t launch_row(int mode, const RowArgs& a, hipStream_t st);
 // mode ROW_UPDATE or ROW_UPDATE_EXACT; a.w is unused (the fused pass forms v
-// from f.u and f.xbar); a.part gets one partial sum per (look, row block)
+// from f.u and f.xbar); a.part gets one partial sum per (look, block)
 hipError_t launch_row_update_mann(int mode, const RowArgs& a, const FuseArgs& f, hipStream_t st);
 hipError_t launch_scatter_full(const SceneTables& s, int looks, const float2* cmp,
                                float2* full, hipStream_t st);
-hipError_t launch_gamma(const SceneTables& s, int looks, const double* part_row,
-                        const double* part_colfwd, const double* part_colinv,
-                        double inv_s2w, double* diag, uint32_t* fault, unsigned* counter, hipStream_t st);
+// nrow, ncol: partial-sum sets per look of the row and the column side
+hipError_t launch_gamma(int nrow, int ncol, int looks, const double* part_row, const double* part_colfwd,
+                        const double* part_colinv, double inv_s2w, double* diag, uint32_t* fault, unsigned* counter, hipStream_t st);
 hipError_t launch_resid_update(const SceneTables& s, int looks, float2* resid,
                                const float2* dfd, const double* diag, double* part,
                                hipStream_t st);
 // h after, mu-residual and ||resid||^2 per look, then (last look done) the
-// summary row diag[looks]; ahy2 may be NULL (mu-residuals 0).
-hipError_t launch_diag_after(const SceneTables& s, int looks, const double* part_upd,
-                             const double* part_resid, double s2w, const double* ahy2, double* diag,
-                             unsigned* counter, hipStream_t st);
+// summary row diag[looks]; ahy2 may be NULL (mu-residuals 0).  nupd, nres:
+// partial sums per look.  With conv_err, the launch also sums the Mann step's
+// `nmace` partials into it (launch_mace_final).
+hipError_t launch_diag_after(int nupd, int nres, int looks, const double* part_upd, const double* part_resid,
+                             double s2w, const double* ahy2, double* diag, unsigned* counter,
+                             const double* part_mace, int nmace, double* conv_err, hipStream_t st);
 // out[i] = a[i] - b[i] over count complex values
 hipError_t launch_csub(size_t count, const float2* a, const float2* b, float2* out, hipStream_t st);
 hipError_t launch_init_r0(size_t n, int looks, float2* mu, float s_mu, float* r0,
@@ -312,6 +345,7 @@ struct BatchLaunch {
     int seg_count[3][kSizeClasses];
     int seg_grid[3][kSizeClasses];
     int nseg[3];
+    int mann_split[kSizeClasses];  // waves per row group in a segment of the fused update pass (1 or 4)
     const float* beta_table;    // device [beta_len]
     int beta_len;
     int* iter;                  // device iteration counter (iterations done)
@@ -322,7 +356,7 @@ hipError_t batch_stage(int stage, const BatchLaunch& b, hipStream_t st);
 hipError_t batch_set_iter(int* iter, int value, hipStream_t st);
 enum BatchStage {
     BS_COL_INV = 0, BS_ROW_GRAD, BS_COL_FWD, BS_GAMMA, BS_ROW_UPDATE, BS_RESID, BS_DIAG,
-    BS_PRIOR, BS_MACE, BS_MACE_FINAL, BS_NEXT_ITER, BS_ROW_UPDATE_MANN
+    BS_PRIOR, BS_MACE, BS_MACE_FINAL, BS_NEXT_ITER, BS_ROW_UPDATE_MANN, BS_FINISH
 };
 
 }  // namespace clampk

@@ -167,12 +167,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) voi
     row_item<NX, ROW_GRAD>(a, blockIdx.y, blockIdx.x, (size_t)blockIdx.y * gridDim.x + blockIdx.x, L, true, bv);
 }
 
-// The update pass with the Mann step fused in: one block per row group,
-// walking every look (row_update_mann).  Held to three waves per SIMD (168
+// The update pass with the Mann step fused in (row_update_mann).  Held to three waves per SIMD (168
 // registers): the per-voxel sums across looks come on top of the update
 // pass's registers, and at four waves (128) the compiler spills 25 of them
 // to scratch inside the look loop.
-template <int NX, int MODE>
+// SHARED: f.split of the block's waves share a row group's looks; otherwise
+// the sharing is known to be none at compile time (as a run-time 1 it cost the
+// 512-point rows 26 spilled scalar registers).
+template <int NX, int MODE, bool SHARED>
 __device__ __forceinline__ void row_upd_mann_block(const RowArgs& a, const FuseArgs& f) {
     __shared__ float2 tw[NX];
     __shared__ int bpos[NX];
@@ -182,19 +184,27 @@ __device__ __forceinline__ void row_upd_mann_block(const RowArgs& a, const FuseA
     __shared__ float keep[mann_lds_floats<NX>()];
     const RowLds L{tw, bpos, bcol, buf};
     const BetaVals bv{a.beta, a.inv_beta, a.k_up, a.k_dn};
-    row_update_mann<NX, MODE>(a, f, blockIdx.x, gridDim.x, L, bv, ups, keep);
+    row_update_mann<NX, MODE>(a, f, SHARED ? f.split : 1, blockIdx.x, gridDim.x, L, bv, ups, keep);
 }
-template <int NX>
+template <int NX, bool SHARED>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) void k_row_upd_mann(RowArgs a,
                                                                                                 FuseArgs f) {
-    row_upd_mann_block<NX, ROW_UPDATE>(a, f);
+    row_upd_mann_block<NX, ROW_UPDATE, SHARED>(a, f);
 }
 // The exact surrogate prox's float64 root solve needs more registers: two
 // waves per SIMD.
 template <int NX>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) void k_row_upd_mann_exact(
     RowArgs a, FuseArgs f) {
-    row_upd_mann_block<NX, ROW_UPDATE_EXACT>(a, f);
+    row_upd_mann_block<NX, ROW_UPDATE_EXACT, true>(a, f);
+}
+
+// ---------------------------------------------------------------------------
+// The passes up to the step size, one block per slice of one look.
+extern __shared__ float2 slice_lds[];
+template <int NX, int NY>
+__global__ __launch_bounds__((SliceGeo<NX, NY>::NT)) void k_slice_grad(SliceArgs a) {
+    slice_grad_item<NX, NY>(a, blockIdx.x, slice_lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -220,7 +230,12 @@ __global__ __launch_bounds__(kBlock) void k_resid(size_t per_look, float2* resid
     block_sum_store<1>(acc, part + (size_t)look * gridDim.x + blockIdx.x);
 }
 
-__global__ __launch_bounds__(kBlock) void k_diag_after(DiagArgs a) { diag_after_item(blockIdx.x, a); }
+// Block l < looks: look l's diagnostics; block `looks` (launched with conv
+// only): the convergence error of the Mann step.
+__global__ __launch_bounds__(kBlock) void k_diag_after(DiagArgs a, const double* part, int blocks, double* conv) {
+    if ((int)blockIdx.x < a.looks) diag_after_item(blockIdx.x, a);
+    else mace_final_item(part, blocks, conv);
+}
 
 __global__ __launch_bounds__(kBlock) void k_csub(size_t count, const float2* a, const float2* b, float2* out) {
     for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < count; i += (size_t)gridDim.x * kBlock) {
@@ -334,11 +349,7 @@ __global__ __launch_bounds__(kBlock) void k_mann_state(size_t n, int looks, int 
 }
 
 __global__ __launch_bounds__(kBlock) void k_mace_final(const double* part, int blocks, double* conv) {
-    double v[2] = {0.0, 0.0};
-    strided_sums<2>(part, blocks, 2, v);
-    __shared__ double tot[2];
-    block_sum_store<2>(v, tot);
-    if (threadIdx.x == 0) conv[0] = tot[1] > 0.0 ? sqrt(tot[0] / tot[1]) : 0.0;
+    mace_final_item(part, blocks, conv);
 }
 
 // ---------------------------------------------------------------------------
@@ -358,6 +369,18 @@ __global__ __launch_bounds__(kBlock) void k_gauss3d(PriorArgs p) {
 // ---------------------------------------------------------------------------
 // Launchers
 #define CLAMP_SIZES(X) X(32) X(64) X(128) X(192) X(256) X(384) X(512)
+
+// Waves sharing a row group's looks in the fused update pass: as many of a
+// block's four as there are looks for, while the grid still fits on the chip
+// at once (three blocks per CU).  Past that the sharing only spreads a block's
+// accesses over more streams: 256x256x64 with 16 looks took 1040 us an
+// iteration with four waves per group against 957 with one; 64x64x32 with 8
+// looks 53 us against 67.
+int mann_split(const SceneTables& s, int looks, int cus) {
+    int split = 1;
+    while (split < 4 && 2 * split <= looks && mann_blocks(s, 2 * split) <= 3 * cus) split *= 2;
+    return split;
+}
 
 static int g_col_grid_cap = 0;
 
@@ -440,14 +463,16 @@ hipError_t launch_row(int mode, const RowArgs& a, hipStream_t st) {
 
 template <int MODE>
 static hipError_t row_update_mann_dispatch(const RowArgs& a, const FuseArgs& f, hipStream_t st) {
-    const dim3 grid((unsigned)row_blocks(a.s));
+    const dim3 grid((unsigned)mann_blocks(a.s, f.split));
     switch (a.s.nx) {
 #define CASE(N)                                                                          \
     case N:                                                                              \
         if constexpr (MODE == ROW_UPDATE_EXACT)                                          \
             hipLaunchKernelGGL((k_row_upd_mann_exact<N>), grid, dim3(kBlock), 0, st, a, f); \
+        else if (f.split == 1)                                                           \
+            hipLaunchKernelGGL((k_row_upd_mann<N, false>), grid, dim3(kBlock), 0, st, a, f); \
         else                                                                             \
-            hipLaunchKernelGGL((k_row_upd_mann<N>), grid, dim3(kBlock), 0, st, a, f);    \
+            hipLaunchKernelGGL((k_row_upd_mann<N, true>), grid, dim3(kBlock), 0, st, a, f); \
         break;
         CLAMP_SIZES(CASE)
 #undef CASE
@@ -474,12 +499,41 @@ hipError_t launch_scatter_full(const SceneTables& s, int looks, const float2* cm
     return hipGetLastError();
 }
 
-hipError_t launch_gamma(const SceneTables& s, int looks, const double* part_row, const double* part_colfwd,
-                          const double* part_colinv, double inv_s2w, double* diag, uint32_t* fault,
-                          unsigned* counter, hipStream_t st) {
-    // with the 3D operator the column-side sums come from the range passes
-    const int ncol = s.K > 0 ? zpass_blocks(s) : col_blocks(s);
-    const GammaArgs a{row_blocks(s), ncol, part_row, part_colfwd, part_colinv, inv_s2w, diag, fault, counter};
+// Sizes of the slice pass and the LDS a block may take (160 KB per CU, less
+// the reduction's static share).  128-point slices fit as well (70 KB of band
+// and as much for the rows of 16 waves) but leave room for one block per CU,
+// whose passes then wait for each other: 128x128x64 with 9 looks took 194 us
+// an iteration against 187 with the three launches, and 128^3 361 against 352.
+#define CLAMP_SLICE_SIZES(X) X(32, 32) X(32, 64) X(64, 32) X(64, 64)
+constexpr size_t kSliceLdsMax = 160 * 1024 - 1024;
+
+bool slice_path(const SceneTables& s) {
+#define CASE(NX, NY) \
+    if (s.nx == NX && s.ny == NY) return slice_lds_bytes<NX, NY>(s.B) <= kSliceLdsMax;
+    CLAMP_SLICE_SIZES(CASE)
+#undef CASE
+    return false;
+}
+
+hipError_t launch_slice_grad(const SliceArgs& a, hipStream_t st) {
+    if (a.looks <= 0) return hipSuccess;
+    const dim3 grid((unsigned)a.looks * (unsigned)a.s.nz);
+#define CASE(NX, NY)                                                                                      \
+    if (a.s.nx == NX && a.s.ny == NY) {                                                                   \
+        const dim3 block(SliceGeo<NX, NY>::NT);                                                           \
+        const unsigned lds = (unsigned)slice_lds_bytes<NX, NY>(a.s.B);                                    \
+        hipLaunchKernelGGL((k_slice_grad<NX, NY>), grid, block, lds, st, a);                              \
+        return hipGetLastError();                                                                         \
+    }
+    CLAMP_SLICE_SIZES(CASE)
+#undef CASE
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_gamma(int nrow, int ncol, int looks, const double* part_row, const double* part_colfwd,
+                        const double* part_colinv, double inv_s2w, double* diag, uint32_t* fault, unsigned* counter,
+                        hipStream_t st) {
+    const GammaArgs a{nrow, ncol, part_row, part_colfwd, part_colinv, inv_s2w, diag, fault, counter};
     hipLaunchKernelGGL(k_gamma, dim3(looks), dim3(kBlock), 0, st, a);
     return hipGetLastError();
 }
@@ -492,10 +546,12 @@ hipError_t launch_resid_update(const SceneTables& s, int looks, float2* resid, c
     return hipGetLastError();
 }
 
-hipError_t launch_diag_after(const SceneTables& s, int looks, const double* pupd, const double* pres,
-                             double s2w, const double* ahy2, double* diag, unsigned* counter, hipStream_t st) {
-    const DiagArgs a{row_blocks(s), resid_blocks(s), looks, pupd, pres, s2w, ahy2, diag, counter};
-    hipLaunchKernelGGL(k_diag_after, dim3(looks), dim3(kBlock), 0, st, a);
+hipError_t launch_diag_after(int nupd, int nres, int looks, const double* pupd, const double* pres, double s2w,
+                             const double* ahy2, double* diag, unsigned* counter, const double* part_mace, int nmace,
+                             double* conv_err, hipStream_t st) {
+    const DiagArgs a{nupd, nres, looks, pupd, pres, s2w, ahy2, diag, counter};
+    hipLaunchKernelGGL(k_diag_after, dim3(looks + (conv_err != nullptr ? 1 : 0)), dim3(kBlock), 0, st, a, part_mace,
+                       nmace, conv_err);
     return hipGetLastError();
 }
 

@@ -433,43 +433,58 @@ __device__ __forceinline__ void row_item(const A& a, int look, int rgroup, size_
 }
 
 // ---------------------------------------------------------------------------
-// Update pass with the Mann step of Alg. 1 fused in: the block walks every
-// look of rows [rgroup * RPB, rgroup * RPB + RPB).  Per look it does what
-// row_item's update does (recompute d, mu += gamma d, the r-update), with the
-// prox point v = u_l + 2 rho xbar_old, and writes u_l' = v - 2 rho r_l; across
-// looks it keeps, per voxel, sum_j upsilon_j r_j and sum_j (r_j - w_bar)^2,
-// where w_bar = sum_j upsilon_j w_j is the average of the Mann state passed
-// in (G(w)), which the previous call left in f.wbar.  After the last look it
+// Update pass with the Mann step of Alg. 1 fused in: every look of a group of
+// rows passes through one block.  Per look it does what row_item's update
+// does (recompute d, mu += gamma d, the r-update), with the prox point v =
+// u_l + 2 rho xbar_old, and writes u_l' = v - 2 rho r_l; across looks it
+// keeps, per voxel, sum_j upsilon_j r_j and sum_j (r_j - w_bar)^2, where
+// w_bar = sum_j upsilon_j w_j is the average of the Mann state passed in
+// (G(w)), which the previous call left in f.wbar.  After the last look it
 // adds the prior agent (its w and H(w)) and writes x_bar = sum_j upsilon_j
 // (2 r_j - w_j) = 2 sum_j upsilon_j r_j - w_bar, the new average w_bar +
-// 2 rho (sum_j upsilon_j r_j - w_bar) and the prior's new w.  Partial sums:
-// sum omega |mu'|^2 per (look, block) into a.part, the convergence error's
-// (sum_j (r_j - w_bar)^2, N w_bar^2) per block into f.part.
+// 2 rho (sum_j upsilon_j r_j - w_bar) and the prior's new w.
+//
+// A group is the 64 / TR rows of one wave.  `split` of the block's four waves
+// (1, 2 or 4) share a group and take its looks in turn, so that the serial
+// chain over the looks is that much shorter (mann_split); their sums are
+// added in wave order through LDS, and each then finishes its share of the
+// voxels.  Partial sums per block: sum omega |mu'|^2 of each look into
+// a.part, the convergence error's (sum_j (r_j - w_bar)^2, N w_bar^2) into f.part.
 template <int NX>
 __host__ __device__ constexpr int mann_lds_floats() {
     return 2 * kBlock * ((NX + row_threads(NX) - 1) / row_threads(NX));
 }
 
 // LDS: ups[64] holds the agent weights, keep[mann_lds_floats<NX>()] each
-// thread's x_bar and w_bar of the previous call ([k][thread], conflict-free),
-// read back at every look instead of held in registers.
+// group's x_bar and w_bar of the previous call ([k][group lane],
+// conflict-free), read back at every look instead of held in registers, and
+// after the looks the waves' sums.
 template <int NX, int MODE, class A, class F>
-__device__ __forceinline__ void row_update_mann(const A& a, const F& f, int rgroup, int nblk,
+__device__ __forceinline__ void row_update_mann(const A& a, const F& f, int split, int blk, int nblk,
                                                 const RowLds& L, BetaVals bv, float* ups, float* keep) {
+    __shared__ double wsum[64][4];                  // [look][wave], at most 64 looks
     constexpr int TR = row_threads(NX);
-    constexpr int RPB = rows_per_block(NX);
+    constexpr int RPW = 64 / TR;                    // rows per wave
     constexpr int PX = (NX + TR - 1) / TR;
     constexpr int PAD = kRowPad;
     constexpr int RS = lds_len<NX, PAD>();
+    // 512-point rows: one barrier per look keeps the block's four rows on the
+    // same look (512x512x64, 8 looks: 1039 us with it, 1048 without); shorter
+    // rows run the waves apart (128^3, 9 looks: 344 us an iteration against 351)
+    constexpr bool kLockstep = NX >= 512;
     const auto& s = a.s;
-    const int tid = threadIdx.x;
-    const int ri = tid / TR, t = tid % TR;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int gpb = 4 / split;                      // groups per block
+    const int gi = wave / split, part = wave % split;
+    const int t = lane % TR;
     const int rows = s.nz * s.ny;
-    const int row = rgroup * RPB + ri;
+    const int row = (blk * gpb + gi) * RPW + lane / TR;
     const bool active = row < rows;
     const size_t n = (size_t)rows * NX;
     const int arow = active ? row : 0;
     const size_t pix = (size_t)arow * NX;
+    const int kst = 64 * gpb, kl = gi * 64 + lane;  // keep's stride and this lane's slot
     for (int i = tid; i < NX; i += kBlock) {
         L.tw[i] = s.tw_x[i];
         L.bpos[i] = s.band_pos[i];
@@ -482,11 +497,13 @@ __device__ __forceinline__ void row_update_mann(const A& a, const F& f, int rgro
 #pragma unroll
         for (int j = 0; j < 64; ++j) ups[j] = f.ups[j];
     }
-    float2* rb = L.buf + ri * RS;
-    float* xo = keep;                  // xo[k * kBlock + tid]
-    float* wb = keep + PX * kBlock;    // wb[k * kBlock + tid]
+    float2* rb = L.buf + (tid / TR) * RS;
+    float* xo = keep;                  // xo[k * kst + kl]
+    float* wb = keep + PX * kst;       // wb[k * kst + kl]
     float sr[PX], e2[PX];
-    {
+#pragma unroll
+    for (int k = 0; k < PX; ++k) sr[k] = e2[k] = 0.f;
+    if (part == 0) {
         // all loads issued before the first is used (samples past the row
         // end and inactive rows read the row's first sample)
         float a0[PX], a1[PX];
@@ -499,14 +516,13 @@ __device__ __forceinline__ void row_update_mann(const A& a, const F& f, int rgro
         }
 #pragma unroll
         for (int k = 0; k < PX; ++k) {
-            xo[k * kBlock + tid] = a0[k];
-            wb[k * kBlock + tid] = a1[k];
-            sr[k] = e2[k] = 0.f;
+            xo[k * kst + kl] = a0[k];
+            wb[k * kst + kl] = a1[k];
         }
     }
     __syncthreads();
     uint32_t fb = 0u;
-    for (int l = 0; l < a.looks; ++l) {
+    for (int l = part; l < a.looks; l += split) {
         const size_t img = (size_t)l * n + pix;
         const size_t band = ((size_t)l * s.nz + arow / s.ny) * s.ny * s.Bs + band_row_off(arow % s.ny, s.ny);
         float2 h[PX];
@@ -550,19 +566,57 @@ __device__ __forceinline__ void row_update_mann(const A& a, const F& f, int rgro
                     const float2 d = make_float2(ahr.x * a.inv_s2w - om * m[k].x, ahr.y * a.inv_s2w - om * m[k].y);
                     const float2 m1 = make_float2(m[k].x + gamma * d.x, m[k].y + gamma * d.y);
                     st_stream(&a.mu[img + x], m1);
-                    const float v = uv[k] + f.two_rho * xo[k * kBlock + tid];
+                    const float v = uv[k] + f.two_rho * xo[k * kst + kl];
                     const float rn = r_update_voxel<MODE>(a, bv, r0, v, m1, fb);
                     st_stream(&a.r[img + x], rn);
                     st_stream(&f.u[img + x], v - f.two_rho * rn);
                     sr[k] += ul * rn;
-                    const float e = rn - wb[k * kBlock + tid];
+                    const float e = rn - wb[k * kst + kl];
                     e2[k] += e * e;
                     wm1 += om * cabs2(m1);
                 }
             }
         }
-        double acc[1] = {wm1};
-        block_sum_store<1>(acc, a.part + (size_t)l * nblk + rgroup);
+        // the wave's share of the look's sum omega |mu'|^2 (no wait for the
+        // other waves here)
+        double acc = wm1;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+        if (lane == 0) wsum[l][wave] = acc;
+        if (kLockstep && split == 1) __syncthreads();
+    }
+    __syncthreads();
+    if (tid < a.looks) {
+        // in wave order; of a group's waves only one took this look
+        double acc = 0.0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+            if (w % split == tid % split) acc += wsum[tid][w];
+        a.part[(size_t)tid * nblk + blk] = acc;
+    }
+    if (split > 1) {
+        // the group's sums over its waves, in wave order, through the row
+        // buffers; wave `part` goes on with the voxels k = part, part + split, ...
+        float* red = reinterpret_cast<float*>(L.buf);
+        static_assert(2 * PX * kBlock * sizeof(float) <= row_lds_floats2<NX>() * sizeof(float2),
+                      "the row buffers hold every thread's sums");
+#pragma unroll
+        for (int k = 0; k < PX; ++k) {
+            red[k * kBlock + tid] = sr[k];
+            red[(PX + k) * kBlock + tid] = e2[k];
+        }
+        __syncthreads();
+        const int t0 = gi * split * 64 + lane;
+#pragma unroll
+        for (int k = 0; k < PX; ++k) {
+            float s0 = red[k * kBlock + t0], s1 = red[(PX + k) * kBlock + t0];
+            for (int w = 1; w < split; ++w) {
+                s0 += red[k * kBlock + t0 + 64 * w];
+                s1 += red[(PX + k) * kBlock + t0 + 64 * w];
+            }
+            sr[k] = s0;
+            e2[k] = s1;
+        }
     }
     const bool prior = f.wprior != nullptr;
     const float up = prior ? ups[a.looks] : 0.f;
@@ -577,6 +631,7 @@ __device__ __forceinline__ void row_update_mann(const A& a, const F& f, int rgro
         const float* wsrc = prior ? f.wprior : f.xbar;
 #pragma unroll
         for (int k = 0; k < PX; ++k) {
+            if ((k & (split - 1)) != part) continue;
             const int x = t + k * TR;
             const size_t i = pix + ((NX % TR == 0 || x < NX) ? x : 0);
             rpv[k] = rsrc[i];
@@ -586,9 +641,10 @@ __device__ __forceinline__ void row_update_mann(const A& a, const F& f, int rgro
     if (active) {
 #pragma unroll
         for (int k = 0; k < PX; ++k) {
+            if ((k & (split - 1)) != part) continue;
             const int x = t + k * TR;
             if (NX % TR == 0 || x < NX) {
-                const float wbk = wb[k * kBlock + tid];
+                const float wbk = wb[k * kst + kl];
                 const float e = rpv[k] - wbk;
                 const float s_r = prior ? sr[k] + up * rpv[k] : sr[k];
                 const float nm = e2[k] + (prior ? e * e : 0.f);
@@ -603,7 +659,7 @@ __device__ __forceinline__ void row_update_mann(const A& a, const F& f, int rgro
     }
     wave_or_fault(fb, a.fault);
     double acc2[2] = {num, den};
-    block_sum_store<2>(acc2, f.part + (size_t)rgroup * 2);
+    block_sum_store<2>(acc2, f.part + (size_t)blk * 2);
 }
 
 // ---------------------------------------------------------------------------
@@ -810,6 +866,207 @@ __device__ __forceinline__ void col_fwd_stream(int first, int count, int stride,
     }
 }
 
+// ---------------------------------------------------------------------------
+// The three passes up to the step size on one slice of one look, for slices
+// whose band fits in LDS: inverse column FFTs of the pupil samples, the
+// gradient row pass, forward column FFTs back onto the pupil.  The band
+// columns live in S (row y, band column b at slice_pos) from the first pass
+// to the last; the only band traffic to memory is the copy the update pass
+// reads.  NY / 8 threads hold a column, NX / 8 a row, both inside one wave, so
+// block barriers stand only between the passes.  Small scenes are bound by
+// the chain of dependent launches, about 4 us each: one iteration of 64x64x32
+// with 8 looks and the Gaussian prior took 87 us and takes 54 us with this
+// pass, the shared looks of row_update_mann and the joined final sums;
+// 32x32x16 with 4 looks, forward agents only, 46 and 30 us.
+template <int NX, int NY>
+struct SliceGeo {
+    static constexpr int TY = NY / 8, TR = NX / 8;      // threads per column, per row
+    static constexpr int CPW = 64 / TY, RPW = 64 / TR;  // columns and rows per wave
+    static constexpr int NT = NX * NY / 8 < 128 ? 128 : NX * NY / 8 > 1024 ? 1024 : NX * NY / 8;
+    static constexpr int NW = NT / 64;
+    static constexpr int RS = lds_len<NX, kRowPad>();
+    static_assert(NY % (NW * RPW) == 0, "the block's waves share the rows evenly");
+};
+
+// Row stride of S: an odd multiple of the columns per wave, at least B, so
+// that the 64 / TY columns of TY consecutive rows spread over the LDS banks;
+// every eighth row shifts by as much again, for the autosort stores, whose
+// rows are eight apart.
+__host__ __device__ inline int slice_stride(int cpw, int B) {
+    const int m = (B + cpw - 1) / cpw;
+    return cpw * (m | 1);
+}
+__host__ __device__ constexpr int slice_pos(int y, int b, int stride, int cpw) { return y * stride + (y >> 3) * cpw + b; }
+
+// Dynamic LDS of the slice pass in bytes: S, the waves' row buffers, the two
+// twiddle tables, the band column tables.
+template <int NX, int NY>
+__host__ __device__ inline size_t slice_lds_bytes(int B) {
+    using G = SliceGeo<NX, NY>;
+    const int st = slice_stride(G::CPW, B);
+    return ((size_t)slice_pos(NY - 1, 0, st, G::CPW) + st + (size_t)G::NW * G::RPW * G::RS + NX + NY) * sizeof(float2) +
+           2 * (size_t)NX * sizeof(int);
+}
+
+// Sums of K doubles over a block of NT threads, in a fixed order; thread 0
+// gets them.
+template <int K, int NT>
+__device__ __forceinline__ void block_sums(double (&v)[K]) {
+    __shared__ double red[K][NT / 64];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_xor(v[k], off);
+    }
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    if (lane == 0) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) red[k][wid] = v[k];
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            double s = 0.0;
+#pragma unroll
+            for (int w = 0; w < NT / 64; ++w) s += red[k][w];
+            v[k] = s;
+        }
+    }
+}
+
+// zl = look * nz + z.  Partial sums, one set per slice: prow (||d||^2, sum
+// omega |d|^2, sum omega |mu|^2), pci (||resid||^2 of the slice), pcf
+// (||A d||^2); pci and pcf may be NULL (3D operator: its range passes sum).
+template <int NX, int NY, class A>
+__device__ __forceinline__ void slice_grad_item(const A& a, int zl, float2* lds) {
+    using G = SliceGeo<NX, NY>;
+    constexpr int TY = G::TY, TR = G::TR, CPW = G::CPW, RPW = G::RPW, NT = G::NT, NW = G::NW, RS = G::RS;
+    const auto& s = a.s;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int B = s.B, st = slice_stride(CPW, B);
+    float2* S = lds;
+    float2* rbuf = S + slice_pos(NY - 1, 0, st, CPW) + st;
+    float2* twx = rbuf + NW * RPW * RS;
+    float2* twy = twx + NX;
+    int* bidx = reinterpret_cast<int*>(twy + NY);  // band column of a column, -1 outside the band
+    int* bcol = bidx + NX;
+    for (int i = tid; i < NX; i += NT) {
+        twx[i] = s.tw_x[i];
+        const int off = s.band_pos[i];  // band_col_off of the column: tile * 16 ny + column in the tile
+        bidx[i] = off < 0 ? -1 : off / (16 * NY) * 16 + (off & 15);
+        const int bc = s.band_cols[i < B ? i : 0];
+        bcol[i] = i < B ? bc : 0;
+    }
+    for (int i = tid; i < NY; i += NT) twy[i] = s.tw_y[i];
+
+    // columns: lane (ct, cc) holds rows ct + 8 k' of column g CPW + cc
+    const int cc = lane % CPW, ct = lane / CPW;
+    const float2* src = a.cmp_in + (size_t)zl * s.P;
+    double r2 = 0.0;
+    // the pointwise streams of the wave's first rows, loaded behind the column pass
+    const int ri = lane / TR, t = lane % TR;
+    float2 m[8];
+    float rp[8];
+    auto load_streams = [&](int y) {
+        const size_t img = ((size_t)zl * NY + y) * NX + t;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            m[k] = a.mu[img + k * TR];
+            rp[k] = a.r[img + k * TR];
+        }
+    };
+    load_streams(wave * RPW + ri);
+    __syncthreads();
+    for (int g = wave; g * CPW < B; g += NW) {
+        const int c = g * CPW + cc;
+        const bool ok = c < B;
+        int pi[8];
+        float2 h[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) pi[k] = ok ? s.pidxb[(size_t)(ct + k * TY) * s.Bs + c] : -1;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) h[k] = src[pi[k] >= 0 ? pi[k] : 0];
+        float f = 0.f;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            if (pi[k] < 0) h[k] = make_float2(0.f, 0.f);
+            f += cabs2(h[k]);
+        }
+        r2 += f;
+        // columns past the band transform zeros in the last column's place of
+        // the row padding: st >= g CPW + CPW
+        const auto pos = [c, st](int y) { return slice_pos(y, c, st, CPW); };
+        fft_regs_at<NY, TY, +1, true, true, true>(h, S, pos, ct, twy);
+        group_sync<true>();
+#pragma unroll
+        for (int k = 0; k < 8; ++k) S[pos(ct + k * TY)] = cscale(h[k], a.scale_y);
+    }
+    __syncthreads();
+
+    // rows: RPW rows per wave and turn
+    float2* rb = rbuf + (wave * RPW + ri) * RS;
+    double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int y0 = wave * RPW; y0 < NY; y0 += NW * RPW) {
+        const int y = y0 + ri;
+        float2 h[8];
+        float2* brow = a.band_out + (size_t)zl * NY * s.Bs + band_row_off(y, NY);
+        float2* srow = S + slice_pos(y, 0, st, CPW);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int b = bidx[t + k * TR];
+            h[k] = b >= 0 ? srow[b] : make_float2(0.f, 0.f);
+            if (b >= 0) st_stream(brow + band_col_off(b, NY), h[k]);
+        }
+        row_fft<NX, TR, +1, kRowPad, true>(h, rb, t, twx);
+        float dd = 0.f, wd = 0.f, wm = 0.f;
+        row_grad_pointwise<NX, TR>(a, h, t, m, rp, dd, wd, wm);
+        acc[0] += dd;
+        acc[1] += wd;
+        acc[2] += wm;
+        if (y0 + NW * RPW < NY) load_streams(y + NW * RPW);
+        row_fft<NX, TR, -1, kRowPad, false>(h, rb, t, twx);
+        for (int b = t; b < B; b += TR) srow[b] = cscale(rb[lds_pos<kRowPad>(bcol[b])], a.scale);
+    }
+    __syncthreads();
+
+    double ad = 0.0;
+    float2* dst = a.cmp_out + (size_t)zl * s.P;
+    for (int g = wave; g * CPW < B; g += NW) {
+        const int c = g * CPW + cc;
+        const bool ok = c < B;
+        int pi[8];
+        float2 h[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) pi[k] = ok ? s.pidxb[(size_t)(ct + k * TY) * s.Bs + c] : -1;
+        const auto pos = [c, st](int y) { return slice_pos(y, c, st, CPW); };
+#pragma unroll
+        for (int k = 0; k < 8; ++k) h[k] = S[pos(ct + k * TY)];
+        fft_regs_at<NY, TY, -1, true, true, true>(h, S, pos, ct, twy);
+        float f = 0.f;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            if (pi[k] >= 0) {
+                const float2 v = cscale(h[k], a.scale_y);
+                dst[pi[k]] = v;
+                f += cabs2(v);
+            }
+        }
+        ad += f;
+    }
+    acc[3] = ad;
+    acc[4] = r2;
+    block_sums<5, NT>(acc);
+    if (tid == 0) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) a.prow[(size_t)zl * 3 + k] = acc[k];
+        if (a.pcf != nullptr) {
+            a.pcf[zl] = acc[3];
+            a.pci[zl] = acc[4];
+        }
+    }
+}
+
 // Column-pass item handles for col_fwd_stream: by pointer (kernel
 // arguments) or by private copy (arguments read from device memory).
 struct ColItemRef {
@@ -937,6 +1194,15 @@ __device__ __forceinline__ void diag_after_item(int look, const DiagArgs& a) {
             for (int k = 3; k < kDiag; ++k) srow[k] = 0.0;
         }
     }
+}
+
+// Convergence error of the Mann step from its block partials.
+__device__ __forceinline__ void mace_final_item(const double* part, int blocks, double* conv) {
+    double v[2] = {0.0, 0.0};
+    strided_sums<2>(part, blocks, 2, v);
+    __shared__ double tot[2];
+    block_sum_store<2>(v, tot);
+    if (threadIdx.x == 0) conv[0] = tot[1] > 0.0 ? sqrt(tot[0] / tot[1]) : 0.0;
 }
 
 // Mann step of voxel i with every agent's w and r in registers (NA >=
