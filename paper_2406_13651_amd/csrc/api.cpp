@@ -861,7 +861,7 @@ clamp_status clamp_fwd_agent_mace(const clamp_plan* plan, int32_t scene, const c
     for (int j = 0; j < params->n_agents; ++j) f.ups[j] = params->upsilon[j];
     f.two_rho = 2.f * params->rho;
     f.n_agents = params->n_agents;
-    f.split = clampk::mann_split(s.tab, L, plan->cus);
+    f.split = params->r_update == CLAMP_R_EXACT ? 1 : clampk::mann_split(s.tab, L, plan->cus);
     const int mode = params->r_update == CLAMP_R_EXACT ? clampk::ROW_UPDATE_EXACT : clampk::ROW_UPDATE;
     hipError_t e = agent_launches(run, agent_row_args(run, w), &f, conv_err, [&](const RowArgs& u) {
         return timed(plan, ST_ROW_UPDATE_MANN, run.stream,

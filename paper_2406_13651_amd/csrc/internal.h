@@ -190,7 +190,7 @@ struct FuseArgs {
     float ups[64];
     float two_rho;
     int n_agents;
-    int split;            // waves that share a row group's looks: 1, 2 or 4 (mann_split)
+    int split;            // waves that share a row group's looks: 1, 2 or 4 (mann_split; exact prox: 1)
 };
 int mann_split(const SceneTables& s, int looks, int cus);
 hipError_t launch_col(int mode, const ColArgs& a, hipStream_t st);

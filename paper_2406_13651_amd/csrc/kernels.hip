@@ -171,10 +171,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) voi
 // registers): the per-voxel sums across looks come on top of the update
 // pass's registers, and at four waves (128) the compiler spills 25 of them
 // to scratch inside the look loop.
-// SHARED: f.split of the block's waves share a row group's looks; otherwise
-// the sharing is known to be none at compile time (as a run-time 1 it cost the
-// 512-point rows 26 spilled scalar registers).
-template <int NX, int MODE, bool SHARED>
+// SPLIT waves share a row group's looks; a compile-time number, as a run-time
+// one cost the 512-point rows 26 spilled scalar registers.
+template <int NX, int MODE, int SPLIT>
 __device__ __forceinline__ void row_upd_mann_block(const RowArgs& a, const FuseArgs& f) {
     __shared__ float2 tw[NX];
     __shared__ int bpos[NX];
@@ -184,19 +183,19 @@ __device__ __forceinline__ void row_upd_mann_block(const RowArgs& a, const FuseA
     __shared__ float keep[mann_lds_floats<NX>()];
     const RowLds L{tw, bpos, bcol, buf};
     const BetaVals bv{a.beta, a.inv_beta, a.k_up, a.k_dn};
-    row_update_mann<NX, MODE>(a, f, SHARED ? f.split : 1, blockIdx.x, gridDim.x, L, bv, ups, keep);
+    row_update_mann<NX, MODE>(a, f, SPLIT, blockIdx.x, gridDim.x, L, bv, ups, keep);
 }
-template <int NX, bool SHARED>
+template <int NX, int SPLIT>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) void k_row_upd_mann(RowArgs a,
                                                                                                 FuseArgs f) {
-    row_upd_mann_block<NX, ROW_UPDATE, SHARED>(a, f);
+    row_upd_mann_block<NX, ROW_UPDATE, SPLIT>(a, f);
 }
 // The exact surrogate prox's float64 root solve needs more registers: two
 // waves per SIMD.
 template <int NX>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) void k_row_upd_mann_exact(
     RowArgs a, FuseArgs f) {
-    row_upd_mann_block<NX, ROW_UPDATE_EXACT, true>(a, f);
+    row_upd_mann_block<NX, ROW_UPDATE_EXACT, 1>(a, f);
 }
 
 // ---------------------------------------------------------------------------
@@ -375,7 +374,7 @@ __global__ __launch_bounds__(kBlock) void k_gauss3d(PriorArgs p) {
 // at once (three blocks per CU).  Past that the sharing only spreads a block's
 // accesses over more streams: 256x256x64 with 16 looks took 1040 us an
 // iteration with four waves per group against 957 with one; 64x64x32 with 8
-// looks 53 us against 67.
+// looks went from 82 us to 54 with the sharing and the joined final sums.
 int mann_split(const SceneTables& s, int looks, int cus) {
     int split = 1;
     while (split < 4 && 2 * split <= looks && mann_blocks(s, 2 * split) <= 3 * cus) split *= 2;
@@ -470,9 +469,11 @@ static hipError_t row_update_mann_dispatch(const RowArgs& a, const FuseArgs& f, 
         if constexpr (MODE == ROW_UPDATE_EXACT)                                          \
             hipLaunchKernelGGL((k_row_upd_mann_exact<N>), grid, dim3(kBlock), 0, st, a, f); \
         else if (f.split == 1)                                                           \
-            hipLaunchKernelGGL((k_row_upd_mann<N, false>), grid, dim3(kBlock), 0, st, a, f); \
+            hipLaunchKernelGGL((k_row_upd_mann<N, 1>), grid, dim3(kBlock), 0, st, a, f); \
+        else if (f.split == 2)                                                           \
+            hipLaunchKernelGGL((k_row_upd_mann<N, 2>), grid, dim3(kBlock), 0, st, a, f); \
         else                                                                             \
-            hipLaunchKernelGGL((k_row_upd_mann<N, true>), grid, dim3(kBlock), 0, st, a, f); \
+            hipLaunchKernelGGL((k_row_upd_mann<N, 4>), grid, dim3(kBlock), 0, st, a, f); \
         break;
         CLAMP_SIZES(CASE)
 #undef CASE

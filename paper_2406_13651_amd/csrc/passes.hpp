@@ -270,7 +270,10 @@ __device__ __forceinline__ void row_fft(float2 (&h)[PX], float2* rb, int t, cons
 // FFT of the band already applied): d = A^H r / sigma_w^2 - omega mu with
 // omega = 1 / (r' + sigma_w^2 / alpha), written back into h, plus the
 // thread's shares of ||d||^2, sum omega |d|^2 and sum omega |mu|^2.
-template <int NX, int TR, int PX, class A>
+// SLICE (the slice pass): |mu|^2 is rounded as the compiler rounds it in the
+// gradient row pass -- the square of x first, in the last sample that of y --
+// so that both report the same sums.
+template <int NX, int TR, bool SLICE = false, int PX, class A>
 __device__ __forceinline__ void row_grad_pointwise(const A& a, float2 (&h)[PX], int t, const float2 (&m)[PX],
                                                    const float (&rp)[PX], float& dd, float& wd, float& wm) {
 #pragma unroll
@@ -284,7 +287,12 @@ __device__ __forceinline__ void row_grad_pointwise(const A& a, float2 (&h)[PX], 
             const float d2 = cabs2(d);
             dd += d2;
             wd += om * d2;
-            wm += om * cabs2(m[k]);
+            if constexpr (SLICE) {
+                const float x = k + 1 < PX ? m[k].x : m[k].y, y = k + 1 < PX ? m[k].y : m[k].x;
+                wm = fmaf(om, fmaf(y, y, x * x), wm);
+            } else {
+                wm += om * cabs2(m[k]);
+            }
         }
     }
 }
@@ -446,10 +454,11 @@ __device__ __forceinline__ void row_item(const A& a, int look, int rgroup, size_
 //
 // A group is the 64 / TR rows of one wave.  `split` of the block's four waves
 // (1, 2 or 4) share a group and take its looks in turn, so that the serial
-// chain over the looks is that much shorter (mann_split); their sums are
-// added in wave order through LDS, and each then finishes its share of the
-// voxels.  Partial sums per block: sum omega |mu'|^2 of each look into
-// a.part, the convergence error's (sum_j (r_j - w_bar)^2, N w_bar^2) into f.part.
+// chain over the looks is that much shorter (mann_split).  After each turn the
+// waves exchange their r_l through the row buffers, and each adds those of
+// its share of the voxels in look order -- the same sums, rounding by
+// rounding, as one wave walking every look -- and finishes that share.
+// Partial sums per block: sum omega |mu'|^2 of each look into a.part, the convergence error's (sum_j (r_j - w_bar)^2, N w_bar^2) into f.part.
 template <int NX>
 __host__ __device__ constexpr int mann_lds_floats() {
     return 2 * kBlock * ((NX + row_threads(NX) - 1) / row_threads(NX));
@@ -470,7 +479,7 @@ __device__ __forceinline__ void row_update_mann(const A& a, const F& f, int spli
     constexpr int RS = lds_len<NX, PAD>();
     // 512-point rows: one barrier per look keeps the block's four rows on the
     // same look (512x512x64, 8 looks: 1039 us with it, 1048 without); shorter
-    // rows run the waves apart (128^3, 9 looks: 344 us an iteration against 351)
+    // rows run the waves apart (128^3, 9 looks: 353 us an iteration against 356)
     constexpr bool kLockstep = NX >= 512;
     const auto& s = a.s;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -522,68 +531,93 @@ __device__ __forceinline__ void row_update_mann(const A& a, const F& f, int spli
     }
     __syncthreads();
     uint32_t fb = 0u;
-    for (int l = part; l < a.looks; l += split) {
-        const size_t img = (size_t)l * n + pix;
-        const size_t band = ((size_t)l * s.nz + arow / s.ny) * s.ny * s.Bs + band_row_off(arow % s.ny, s.ny);
-        float2 h[PX];
-        {
-            float2 bin[PX];
-            int bp[PX];
+    // the wave's row buffers, which also take its r_l (rx[k * 64 + lane])
+    float* rx = reinterpret_cast<float*>(rb) - (lane / TR) * 2 * RS;
+    static_assert(PX * 64 * sizeof(float) <= RPW * RS * sizeof(float2), "a wave's row buffers hold its r_l");
+    for (int l0 = 0; l0 < a.looks; l0 += split) {
+        const int l = l0 + part;
+        if (l < a.looks) {
+            const size_t img = (size_t)l * n + pix;
+            const size_t band = ((size_t)l * s.nz + arow / s.ny) * s.ny * s.Bs + band_row_off(arow % s.ny, s.ny);
+            float2 h[PX];
+            {
+                float2 bin[PX];
+                int bp[PX];
 #pragma unroll
-            for (int k = 0; k < PX; ++k) {
-                const int x = t + k * TR;
-                bp[k] = (active && (NX % TR == 0 || x < NX)) ? L.bpos[x] : -1;
-                bin[k] = ld_stream(a.band_in + band + (bp[k] >= 0 ? bp[k] : 0));
+                for (int k = 0; k < PX; ++k) {
+                    const int x = t + k * TR;
+                    bp[k] = (active && (NX % TR == 0 || x < NX)) ? L.bpos[x] : -1;
+                    bin[k] = ld_stream(a.band_in + band + (bp[k] >= 0 ? bp[k] : 0));
+                }
+#pragma unroll
+                for (int k = 0; k < PX; ++k) h[k] = bp[k] >= 0 ? bin[k] : make_float2(0.f, 0.f);
             }
+            row_fft<NX, TR, +1, PAD, true>(h, rb, t, L.tw);
+            float2 m[PX];
+            float rp[PX], uv[PX];
+            if (active) {
 #pragma unroll
-            for (int k = 0; k < PX; ++k) h[k] = bp[k] >= 0 ? bin[k] : make_float2(0.f, 0.f);
-        }
-        row_fft<NX, TR, +1, PAD, true>(h, rb, t, L.tw);
-        float2 m[PX];
-        float rp[PX], uv[PX];
-        if (active) {
-#pragma unroll
-            for (int k = 0; k < PX; ++k) {
-                const int x = t + k * TR;
-                if (NX % TR == 0 || x < NX) {
-                    m[k] = ld_stream(&a.mu[img + x]);
-                    rp[k] = ld_stream(&a.r[img + x]);
-                    uv[k] = ld_stream(&f.u[img + x]);
+                for (int k = 0; k < PX; ++k) {
+                    const int x = t + k * TR;
+                    if (NX % TR == 0 || x < NX) {
+                        m[k] = ld_stream(&a.mu[img + x]);
+                        rp[k] = ld_stream(&a.r[img + x]);
+                        uv[k] = ld_stream(&f.u[img + x]);
+                    }
                 }
             }
+            const float gamma = (float)a.diag[(size_t)l * kDiag];
+            const float ul = ups[l];
+            float wm1 = 0.f;
+            if (active) {
+#pragma unroll
+                for (int k = 0; k < PX; ++k) {
+                    const int x = t + k * TR;
+                    if (NX % TR == 0 || x < NX) {
+                        const float2 ahr = cscale(h[k], a.scale);
+                        const float r0 = rp[k];
+                        const float om = 1.f / (r0 + a.floor_w);
+                        const float2 d = make_float2(ahr.x * a.inv_s2w - om * m[k].x, ahr.y * a.inv_s2w - om * m[k].y);
+                        const float2 m1 = make_float2(m[k].x + gamma * d.x, m[k].y + gamma * d.y);
+                        st_stream(&a.mu[img + x], m1);
+                        const float v = uv[k] + f.two_rho * xo[k * kst + kl];
+                        const float rn = r_update_voxel<MODE>(a, bv, r0, v, m1, fb);
+                        st_stream(&a.r[img + x], rn);
+                        st_stream(&f.u[img + x], v - f.two_rho * rn);
+                        if (split == 1) {
+                            sr[k] = fmaf(ul, rn, sr[k]);
+                            const float e = rn - wb[k * kst + kl];
+                            e2[k] = fmaf(e, e, e2[k]);
+                        } else {
+                            rx[k * 64 + lane] = rn;  // the transform's readers of the row are this wave
+                        }
+                        wm1 += om * cabs2(m1);
+                    }
+                }
+            }
+            // the wave's share of the look's sum omega |mu'|^2 (no wait for the
+            // other waves here)
+            double acc = wm1;
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+            if (lane == 0) wsum[l][wave] = acc;
+            if (kLockstep && split == 1) __syncthreads();
         }
-        const float gamma = (float)a.diag[(size_t)l * kDiag];
-        const float ul = ups[l];
-        float wm1 = 0.f;
-        if (active) {
+        if (split > 1) {
+            __syncthreads();
 #pragma unroll
             for (int k = 0; k < PX; ++k) {
-                const int x = t + k * TR;
-                if (NX % TR == 0 || x < NX) {
-                    const float2 ahr = cscale(h[k], a.scale);
-                    const float r0 = rp[k];
-                    const float om = 1.f / (r0 + a.floor_w);
-                    const float2 d = make_float2(ahr.x * a.inv_s2w - om * m[k].x, ahr.y * a.inv_s2w - om * m[k].y);
-                    const float2 m1 = make_float2(m[k].x + gamma * d.x, m[k].y + gamma * d.y);
-                    st_stream(&a.mu[img + x], m1);
-                    const float v = uv[k] + f.two_rho * xo[k * kst + kl];
-                    const float rn = r_update_voxel<MODE>(a, bv, r0, v, m1, fb);
-                    st_stream(&a.r[img + x], rn);
-                    st_stream(&f.u[img + x], v - f.two_rho * rn);
-                    sr[k] += ul * rn;
+                if ((k & (split - 1)) != part) continue;
+                for (int w = 0; w < split && l0 + w < a.looks; ++w) {
+                    // the group's wave w: its buffers lie w - part waves from this one's
+                    const float rn = rx[(w - part) * (2 * RPW * RS) + k * 64 + lane];
+                    sr[k] = fmaf(ups[l0 + w], rn, sr[k]);
                     const float e = rn - wb[k * kst + kl];
-                    e2[k] += e * e;
-                    wm1 += om * cabs2(m1);
+                    e2[k] = fmaf(e, e, e2[k]);
                 }
             }
+            __syncthreads();  // the buffers are free for the next turn's transforms
         }
-        // the wave's share of the look's sum omega |mu'|^2 (no wait for the
-        // other waves here)
-        double acc = wm1;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-        if (lane == 0) wsum[l][wave] = acc;
-        if (kLockstep && split == 1) __syncthreads();
     }
     __syncthreads();
     if (tid < a.looks) {
@@ -593,30 +627,6 @@ __device__ __forceinline__ void row_update_mann(const A& a, const F& f, int spli
         for (int w = 0; w < 4; ++w)
             if (w % split == tid % split) acc += wsum[tid][w];
         a.part[(size_t)tid * nblk + blk] = acc;
-    }
-    if (split > 1) {
-        // the group's sums over its waves, in wave order, through the row
-        // buffers; wave `part` goes on with the voxels k = part, part + split, ...
-        float* red = reinterpret_cast<float*>(L.buf);
-        static_assert(2 * PX * kBlock * sizeof(float) <= row_lds_floats2<NX>() * sizeof(float2),
-                      "the row buffers hold every thread's sums");
-#pragma unroll
-        for (int k = 0; k < PX; ++k) {
-            red[k * kBlock + tid] = sr[k];
-            red[(PX + k) * kBlock + tid] = e2[k];
-        }
-        __syncthreads();
-        const int t0 = gi * split * 64 + lane;
-#pragma unroll
-        for (int k = 0; k < PX; ++k) {
-            float s0 = red[k * kBlock + t0], s1 = red[(PX + k) * kBlock + t0];
-            for (int w = 1; w < split; ++w) {
-                s0 += red[k * kBlock + t0 + 64 * w];
-                s1 += red[(PX + k) * kBlock + t0 + 64 * w];
-            }
-            sr[k] = s0;
-            e2[k] = s1;
-        }
     }
     const bool prior = f.wprior != nullptr;
     const float up = prior ? ups[a.looks] : 0.f;
@@ -871,9 +881,10 @@ __device__ __forceinline__ void col_fwd_stream(int first, int count, int stride,
 // whose band fits in LDS: inverse column FFTs of the pupil samples, the
 // gradient row pass, forward column FFTs back onto the pupil.  The band
 // columns live in S (row y, band column b at slice_pos) from the first pass
-// to the last; the only band traffic to memory is the copy the update pass
-// reads.  NY / 8 threads hold a column, NX / 8 a row, both inside one wave, so
-// block barriers stand only between the passes.  Small scenes are bound by
+// to the last, with the arithmetic and the float32 groups of the partial sums
+// of the three passes; the only band traffic to memory is the copy the update
+// pass reads.  NY / 8 threads hold a column, NX / 8 a row, both inside one
+// wave, so block barriers stand only between the passes.  Small scenes are bound by
 // the chain of dependent launches, about 4 us each: one iteration of 64x64x32
 // with 8 looks and the Gaussian prior took 87 us and takes 54 us with this
 // pass, the shared looks of row_update_mann and the joined final sums;
@@ -896,7 +907,9 @@ __host__ __device__ inline int slice_stride(int cpw, int B) {
     const int m = (B + cpw - 1) / cpw;
     return cpw * (m | 1);
 }
-__host__ __device__ constexpr int slice_pos(int y, int b, int stride, int cpw) { return y * stride + (y >> 3) * cpw + b; }
+__host__ __device__ constexpr int slice_pos(int y, int b, int stride, int cpw) {
+    return y * stride + (y >> 3) * cpw + b;
+}
 
 // Dynamic LDS of the slice pass in bytes: S, the waves' row buffers, the two
 // twiddle tables, the band column tables.
@@ -987,13 +1000,26 @@ __device__ __forceinline__ void slice_grad_item(const A& a, int zl, float2* lds)
         for (int k = 0; k < 8; ++k) pi[k] = ok ? s.pidxb[(size_t)(ct + k * TY) * s.Bs + c] : -1;
 #pragma unroll
         for (int k = 0; k < 8; ++k) h[k] = src[pi[k] >= 0 ? pi[k] : 0];
-        float f = 0.f;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
+        for (int k = 0; k < 8; ++k)
             if (pi[k] < 0) h[k] = make_float2(0.f, 0.f);
-            f += cabs2(h[k]);
+        // ||resid||^2 of the column: samples p0 + lane + 16 k in float32 sums
+        // per lane of 16, rounded as the inverse column pass rounds them
+        if (c < B) {
+            const int p0 = s.col_off[c], p1 = s.col_off[c + 1];
+            for (int ln = ct; ln < 16; ln += TY) {
+                float f = 0.f;
+#pragma unroll
+                for (int k = 0; k < NY / 16; ++k) {
+                    const int p = p0 + ln + 16 * k;
+                    if (p < p1) {
+                        const float2 v = src[p];
+                        f += fmaf(v.y, v.y, v.x * v.x);
+                    }
+                }
+                r2 += f;
+            }
         }
-        r2 += f;
         // columns past the band transform zeros in the last column's place of
         // the row padding: st >= g CPW + CPW
         const auto pos = [c, st](int y) { return slice_pos(y, c, st, CPW); };
@@ -1020,7 +1046,7 @@ __device__ __forceinline__ void slice_grad_item(const A& a, int zl, float2* lds)
         }
         row_fft<NX, TR, +1, kRowPad, true>(h, rb, t, twx);
         float dd = 0.f, wd = 0.f, wm = 0.f;
-        row_grad_pointwise<NX, TR>(a, h, t, m, rp, dd, wd, wm);
+        row_grad_pointwise<NX, TR, true>(a, h, t, m, rp, dd, wd, wm);
         acc[0] += dd;
         acc[1] += wd;
         acc[2] += wm;
@@ -1034,25 +1060,29 @@ __device__ __forceinline__ void slice_grad_item(const A& a, int zl, float2* lds)
     float2* dst = a.cmp_out + (size_t)zl * s.P;
     for (int g = wave; g * CPW < B; g += NW) {
         const int c = g * CPW + cc;
-        const bool ok = c < B;
-        int pi[8];
         float2 h[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) pi[k] = ok ? s.pidxb[(size_t)(ct + k * TY) * s.Bs + c] : -1;
         const auto pos = [c, st](int y) { return slice_pos(y, c, st, CPW); };
 #pragma unroll
         for (int k = 0; k < 8; ++k) h[k] = S[pos(ct + k * TY)];
-        fft_regs_at<NY, TY, -1, true, true, true>(h, S, pos, ct, twy);
-        float f = 0.f;
+        fft_regs_at<NY, TY, -1, true, false, true>(h, S, pos, ct, twy);
+        // the column's pupil samples p0 + lane + 16 k, float32 sums per lane
+        // of 16, as the forward column pass stores and sums them
+        if (c < B) {
+            const int p0 = s.col_off[c], p1 = s.col_off[c + 1];
+            for (int ln = ct; ln < 16; ln += TY) {
+                float f = 0.f;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            if (pi[k] >= 0) {
-                const float2 v = cscale(h[k], a.scale_y);
-                dst[pi[k]] = v;
-                f += cabs2(v);
+                for (int k = 0; k < NY / 16; ++k) {
+                    const int p = p0 + ln + 16 * k;
+                    if (p < p1) {
+                        const float2 v = cscale(S[pos(s.row_idx[p])], a.scale_y);
+                        dst[p] = v;
+                        f += cabs2(v);
+                    }
+                }
+                ad += f;
             }
         }
-        ad += f;
     }
     acc[3] = ad;
     acc[4] = r2;
