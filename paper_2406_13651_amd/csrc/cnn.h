@@ -7,12 +7,20 @@
 
 namespace clampk {
 
-// Epilogues of the convolution: RELU stores ReLU(y + b); FINAL the one-channel
+// Epilogues of the convolution: RELU stores ReLU(y + b); RELU_BITS does and
+// also stores which outputs are positive (mask_out); FINAL the one-channel
 // output layer x + m (y + b) in fp32; DGRAD the backward-data product masked
-// by the ReLU pattern of relu_src; RAW stores y unchanged (pre-activations
-// before batch normalisation, or a backward-data product through a layer
-// input that is no ReLU output).
-enum ConvEpi { EPI_RELU = 0, EPI_FINAL = 1, EPI_DGRAD = 2, EPI_RAW = 3 };
+// by the ReLU pattern of the layer input (mask); RAW stores y unchanged
+// (pre-activations before batch normalisation, or a backward-data product
+// through a layer input that is no ReLU output).
+enum ConvEpi { EPI_RELU = 0, EPI_FINAL = 1, EPI_DGRAD = 2, EPI_RAW = 3, EPI_RELU_BITS = 4 };
+
+// ReLU patterns: two 16-bit words per voxel; bit 8 p + j of word h is set
+// where channel 16 p + 8 h + j (p, h = 0, 1; j = 0..7) is positive.  A lane of
+// the convolutions holds the channels of one word.  4 bytes per voxel where
+// the activation itself takes 64: a training step at 24 x 32 x 64 x 64 with
+// masks from the activations 3325 us, from the patterns 3258 us (U-Net, 24 x
+// 32 x 32 x 128: 4409 and 4358 us).
 
 struct ConvArgs {
     int nvol, nz, ny, nx;          // nx a multiple of 32
@@ -20,21 +28,22 @@ struct ConvArgs {
     int span;                      // output tile-slices per block (set by cnn_conv)
     const uint16_t* in;            // bf16 [voxel][CIN]
     const uint16_t* wq;            // bf16 weight fragments [9][kQ][2][32][8] (cnn_prep)
-    const float* bias;             // fp32 [32] (EPI_RELU, EPI_FINAL)
-    uint16_t* out;                 // bf16 [voxel][32] (EPI_RELU, EPI_DGRAD)
+    const float* bias;             // fp32 [32] (EPI_RELU, EPI_RELU_BITS, EPI_FINAL)
+    uint16_t* out;                 // bf16 [voxel][32]
     float* out_f32;                // fp32 [voxel] (EPI_FINAL)
     const float* xin;              // fp32 [voxel] residual input (EPI_FINAL), the input (first layer)
     const float* scale;            // device scalar m of the output (EPI_FINAL), of the input (first layer); NULL = 1
-    const uint16_t* relu_src;      // bf16 [voxel][32]: ReLU mask source (EPI_DGRAD)
+    const uint16_t* mask;          // ReLU pattern of the layer input (EPI_DGRAD)
+    uint16_t* mask_out;            // ReLU pattern of the output (EPI_RELU_BITS)
 };
 
 struct WgradArgs {
     int nvol, nz, ny, nx;          // nx a multiple of 32
     int tiles_x, tiles_y;          // item tiles of 32 x-voxels and 8 rows (set by cnn_wgrad)
     int zc, zchunks, items;        // range slices per item, chunks per volume, items (set by cnn_wgrad)
-    const uint16_t* act;           // bf16 [voxel][CA]: the layer input
-    const uint16_t* g;             // bf16 [voxel][CG]: the gradient of the layer output
-    float* part;                   // fp32 [2 * grid][28][32][32] partial sums (cnn_wgrad_part_bytes)
+    const uint16_t* act;           // bf16 [voxel][32]: the layer input
+    const uint16_t* g;             // bf16 [voxel][32]: the gradient of the layer output
+    float* part;                   // fp32 [grid][28][32][32] partial sums (cnn_wgrad_part_bytes)
 };
 
 // cin = 1 with EPI_RELU: the first layer from the fp32 volume (xin, scale;
@@ -47,12 +56,19 @@ size_t cnn_wq_elems(int cinp);
 hipError_t cnn_pack(const float* x, const float* scale, long nvox, uint16_t* x8, hipStream_t st);
 int cnn_reduce_blocks(long nvox);
 hipError_t cnn_mean(const float* x, long nvox, double* part, float* mean, hipStream_t st);
-hipError_t cnn_loss(const float* out, const float* target, long nvox, uint16_t* g8, double* part, double* loss,
-                    hipStream_t st);
+// Squared error, and its gradient in fp32 (g1) and in the 8-channel bf16 form (g8).
+hipError_t cnn_loss(const float* out, const float* target, long nvox, uint16_t* g8, float* g1, double* part,
+                    double* loss, hipStream_t st);
 int cnn_wgrad_grid();
 size_t cnn_wgrad_part_bytes();
-// Weight gradient gw[27][cin][cout] and bias gradient gb[cout] of one layer.
-hipError_t cnn_wgrad(int ca, int cg, WgradArgs a, int cin, int cout, float* gw, float* gb, hipStream_t st);
+// Weight gradient gw[27][32][32] and bias gradient gb[32] of one layer.
+hipError_t cnn_wgrad(WgradArgs a, float* gw, float* gb, hipStream_t st);
+// The same for a layer with one channel on one side: x one-channel fp32
+// (rounded to bf16), y bf16 [voxel][32].  first = 1: x the layer input, y the
+// output gradient, gw [27][1][32], gb [32]; first = 0: x the output gradient,
+// y the layer input, gw [27][32][1], gb [1].  part: cnn_wgrad_part_bytes.
+hipError_t cnn_wgrad_one(int first, int nvol, int nz, int ny, int nx, const float* x, const uint16_t* y, float* part,
+                         float* gw, float* gb, hipStream_t st);
 // Adam step with gradient-norm clipping; clip: device float[kClipFloats],
 // 8-byte aligned: the state clip[0..1] (zeroed with the parameters, see
 // k_grad_clip), then kNormBlocks float64 partial sums of the squared norm.

@@ -55,12 +55,25 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, v);
 }
 
-// Mask of a dword of two bf16 ReLU outputs: each half is all ones when that
-// value is > 0 (sign clear, not zero), else zero.
-__device__ __forceinline__ uint32_t relu_keep2(uint32_t k) {
-    const uint32_t lo = ((k & 0x8000u) == 0u && (k & 0x7fffu) != 0u) ? 0x0000ffffu : 0u;
-    const uint32_t hi = ((k & 0x80000000u) == 0u && (k & 0x7fff0000u) != 0u) ? 0xffff0000u : 0u;
-    return lo | hi;
+// Positive values of a run of eight bf16 ReLU outputs (channels 0..7 in
+// dword order) as bits 0..7.
+typedef unsigned short v2us __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t relu_bits8(const v4u& q) {
+    uint32_t m = 0u;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        // each half: 1 unless zero (a ReLU output has no sign but -0's)
+        const v2us v = __builtin_bit_cast(v2us, (uint32_t)(q[k] & 0x7fff7fffu));
+        m |= __builtin_bit_cast(uint32_t, __builtin_elementwise_min(v, v2us{1, 1})) << (2 * k);
+    }
+    return (m | (m >> 15)) & 0xffu;  // low halves: even bits, high halves: odd bits
+}
+// Mask of the dword of channels 2 k, 2 k + 1 of run p from a ReLU pattern
+// word (p, k constant): all ones where the bit is set.
+__device__ __forceinline__ uint32_t relu_keep(uint32_t w, int p, int k) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_sbfe((int)w, 8 * p + 2 * k, 1);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_sbfe((int)w, 8 * p + 2 * k + 1, 1);
+    return (lo & 0xffffu) | (hi & 0xffff0000u);
 }
 
 // Row index of the MFMA output register i of lane l (the column is l % 32).
@@ -310,7 +323,8 @@ constexpr int conv_threads() { return 64 * kTileRows / RPW; }
 
 template <int CIN, int EPI, int RPW>
 __global__ __launch_bounds__(conv_threads<RPW>(), 1) void k_conv(ConvArgs a) {
-    static_assert(EPI == EPI_RELU || EPI == EPI_DGRAD || EPI == EPI_RAW, "the final layer runs in k_conv_final");
+    static_assert(EPI != EPI_FINAL, "the final layer runs in k_conv_final");
+    constexpr bool kRelu = EPI == EPI_RELU || EPI == EPI_RELU_BITS;
     constexpr int NT = conv_threads<RPW>();
     constexpr int NRD = RPW + 5;  // LDS reads of one stage
     using G = TileGeo<CIN, NT>;
@@ -338,7 +352,7 @@ __global__ __launch_bounds__(conv_threads<RPW>(), 1) void k_conv(ConvArgs a) {
     // output channel of accumulator register i: (i / 4) 8 + 4 h + i % 4
     float bias_r[16];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) bias_r[i] = EPI == EPI_RELU ? a.bias[(i >> 2) * 8 + 4 * h + (i & 3)] : 0.f;
+    for (int i = 0; i < 16; ++i) bias_r[i] = kRelu ? a.bias[(i >> 2) * 8 + 4 * h + (i & 3)] : 0.f;
 
     long t = (long)blockIdx.x * a.span;
     const long total = (long)a.nvol * a.tiles_x * a.tiles_y * a.nz;
@@ -367,7 +381,11 @@ __global__ __launch_bounds__(conv_threads<RPW>(), 1) void k_conv(ConvArgs a) {
                 const int y = y0 + RPW * wave + r;
                 return y < a.ny ? (uint32_t)((y * a.nx + x0 + m) * 64 + 16 * h + 32 * p) : kBufferOutside;
             };
-            v4u keep[RPW][2];  // backward-data pass: ReLU mask of the layer input at the outputs
+            auto mask_off = [&](int r) {
+                const int y = y0 + RPW * wave + r;
+                return y < a.ny ? (uint32_t)((y * a.nx + x0 + m) * 4 + 2 * h) : kBufferOutside;
+            };
+            uint32_t keep[RPW];  // backward-data pass: ReLU pattern of the layer input at the outputs
             ConvFrag<RPW> f[2];
             // dz = 0: input z - 1
             frag_load<CIN, RPW>(ring[old], wsh, 0, 0, wave, m, h, f[0]);
@@ -390,11 +408,10 @@ __global__ __launch_bounds__(conv_threads<RPW>(), 1) void k_conv(ConvArgs a) {
             tile_fetch<CIN, NT>(a, in, z + 2, y0, x0, pre, z + 1 < z1);
             if constexpr (EPI == EPI_DGRAD) {
                 const __amdgpu_buffer_rsrc_t keep_rs = __builtin_amdgcn_make_buffer_rsrc(
-                    const_cast<uint16_t*>(a.relu_src) + slice_off * 32, 0, slice_bytes, kBufferWord3);
+                    const_cast<uint16_t*>(a.mask) + slice_off * 2, 0, slice_bytes / 16, kBufferWord3);
 #pragma unroll
                 for (int r = 0; r < RPW; ++r)
-#pragma unroll
-                    for (int p = 0; p < 2; ++p) keep[r][p] = __builtin_amdgcn_raw_buffer_load_b128(keep_rs, out_off(r, p), 0, 0);
+                    keep[r] = __builtin_amdgcn_raw_buffer_load_b16(keep_rs, mask_off(r), 0, 0);
             }
             __builtin_amdgcn_sched_group_barrier(0x100, NRD, 0);
 #pragma unroll
@@ -435,18 +452,24 @@ __global__ __launch_bounds__(conv_threads<RPW>(), 1) void k_conv(ConvArgs a) {
             // wait for its prefetched slice need not wait for them.
             const __amdgpu_buffer_rsrc_t out_rs =
                 __builtin_amdgcn_make_buffer_rsrc(a.out + slice_off * 32, 0, slice_bytes, kBufferWord3);
+            const __amdgpu_buffer_rsrc_t bits_rs = __builtin_amdgcn_make_buffer_rsrc(
+                EPI == EPI_RELU_BITS ? a.mask_out + slice_off * 2 : nullptr, 0, slice_bytes / 16, kBufferWord3);
 #pragma unroll
             for (int r = 0; r < RPW; ++r) {
+                uint32_t bits = 0u;
 #pragma unroll
                 for (int p = 0; p < 2; ++p) {
                     const uint32_t off = out_off(r, p);
-                    v4u q = out_run<EPI == EPI_RELU>(acc[r], p, bias_r);
+                    v4u q = out_run<kRelu>(acc[r], p, bias_r);
                     if constexpr (EPI == EPI_DGRAD) {
 #pragma unroll
-                        for (int k = 0; k < 4; ++k) q[k] &= relu_keep2(keep[r][p][k]);
+                        for (int k = 0; k < 4; ++k) q[k] &= relu_keep(keep[r], p, k);
                     }
+                    if constexpr (EPI == EPI_RELU_BITS) bits |= relu_bits8(q) << (8 * p);
                     __builtin_amdgcn_raw_buffer_store_b128(q, out_rs, off, 0, 0);
                 }
+                if constexpr (EPI == EPI_RELU_BITS)
+                    __builtin_amdgcn_raw_buffer_store_b16((uint16_t)bits, bits_rs, mask_off(r), 0, 0);
             }
         }
     }
@@ -784,7 +807,7 @@ __global__ __launch_bounds__(kCnnBlock) void k_mean_final(const double* part, in
 
 // Squared error partials and the output gradient 2 (out - t) / nvox.
 __global__ __launch_bounds__(kCnnBlock) void k_loss(const float* out, const float* target, long nvox, uint16_t* g8,
-                                                    double* part) {
+                                                    float* g1, double* part) {
     const float c = (float)(2.0 / (double)nvox);
     double s = 0.0;
     for (long v = (long)blockIdx.x * kCnnBlock + threadIdx.x; v < nvox; v += (long)gridDim.x * kCnnBlock) {
@@ -793,6 +816,7 @@ __global__ __launch_bounds__(kCnnBlock) void k_loss(const float* out, const floa
         uint4 q = make_uint4(0u, 0u, 0u, 0u);
         q.x = f2bf(c * r);
         reinterpret_cast<uint4*>(g8)[v] = q;
+        g1[v] = c * r;
     }
     double a[1] = {s};
     cnn_block_sum<1>(a, part + blockIdx.x);
@@ -862,16 +886,13 @@ __device__ __forceinline__ void transpose8(const uint32_t (&in)[8][4], uint32_t 
 }
 
 // Loads 8 voxels (x, x + 1, .., x + 7 of one row) x 8 channels (group cg) of
-// a channels-last tensor with C stored channels.  Where `ok` is false (or the
-// group is past C) the lanes read the tensor's first 16 bytes instead, and
+// a channels-last tensor.  Where `ok` is false the lanes read the tensor's first 16 bytes instead, and
 // the returned flag is false: the caller zeroes them with mask8x8 when it
 // consumes them, so that nothing waits on the loads before then.
-template <int C>
 __device__ __forceinline__ bool load8x8(const uint16_t* base, long vox0, int cg, bool ok, uint32_t (&v)[8][4]) {
-    ok = ok && cg * 8 < C;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        const uint4 q = *reinterpret_cast<const uint4*>(base + (ok ? (vox0 + e) * C + cg * 8 : 0));
+        const uint4 q = *reinterpret_cast<const uint4*>(base + (ok ? (vox0 + e) * 32 + cg * 8 : 0));
         v[e][0] = q.x;
         v[e][1] = q.y;
         v[e][2] = q.z;
@@ -907,7 +928,7 @@ __device__ __forceinline__ uint4 shifted_chunk(uint4 c, uint32_t before, uint32_
     return q;
 }
 
-template <int TG, int CA, int CG>
+template <int TG>
 __device__ __forceinline__ void wgrad_block(const WgradArgs& a, uint4 (*act)[32 * kActPlane4],
                                             uint32_t (*halo)[kHaloSlot], uint4 (*gt)[32 * kGPlane4], int wave) {
     constexpr int T0 = 7 * TG;
@@ -948,12 +969,12 @@ __device__ __forceinline__ void wgrad_block(const WgradArgs& a, uint4 (*act)[32 
         auto fetch_act = [&](int zin) {
             const int y = y0 - 1 + a_ys, x = x0 - 8 + 8 * a_xc;
             const bool ok = u < 240 && zin >= 0 && zin < a.nz && y >= 0 && y < a.ny && x >= 0 && x < a.nx;
-            pf_ok = load8x8<CA>(a.act, ok ? vol_off + ((long)zin * a.ny + y) * a.nx + x : 0, a_cg, ok, pf);
+            pf_ok = load8x8(a.act, ok ? vol_off + ((long)zin * a.ny + y) * a.nx + x : 0, a_cg, ok, pf);
         };
         auto fetch_g = [&](int zz) {
             const int y = y0 + g_r, x = x0 + 8 * g_xc;
             const bool ok = gu >= 0 && gu < 128 && zz < a.nz && y < a.ny;
-            pf_ok = load8x8<CG>(a.g, ok ? vol_off + ((long)zz * a.ny + y) * a.nx + x : 0, g_cg, ok, pf);
+            pf_ok = load8x8(a.g, ok ? vol_off + ((long)zz * a.ny + y) * a.nx + x : 0, g_cg, ok, pf);
         };
         auto store_act = [&](int zin) {
             if (u < 240) {
@@ -1094,17 +1115,16 @@ __device__ __forceinline__ void wgrad_block(const WgradArgs& a, uint4 (*act)[32 
     }
 }
 
-template <int CA, int CG>
 __global__ __launch_bounds__(kWgBlock, 1) void k_wgrad(WgradArgs a) {
     __shared__ uint4 act[4][32 * kActPlane4];
     __shared__ uint32_t halo[4][kHaloSlot];
     __shared__ uint4 gt[2][32 * kGPlane4];
     const int wave = threadIdx.x >> 6;
     switch (wave >> 1) {
-        case 0: wgrad_block<0, CA, CG>(a, act, halo, gt, wave); break;
-        case 1: wgrad_block<1, CA, CG>(a, act, halo, gt, wave); break;
-        case 2: wgrad_block<2, CA, CG>(a, act, halo, gt, wave); break;
-        default: wgrad_block<3, CA, CG>(a, act, halo, gt, wave); break;
+        case 0: wgrad_block<0>(a, act, halo, gt, wave); break;
+        case 1: wgrad_block<1>(a, act, halo, gt, wave); break;
+        case 2: wgrad_block<2>(a, act, halo, gt, wave); break;
+        default: wgrad_block<3>(a, act, halo, gt, wave); break;
     }
 }
 
@@ -1113,33 +1133,194 @@ __global__ __launch_bounds__(kWgBlock, 1) void k_wgrad(WgradArgs a) {
 // consecutive positions p = t * 1024 + co * 32 + ci; thread (p, l) sums
 // chunks l, l + 16, ... in order, then the 16 partial sums are added in order
 // (a fixed summation order, so runs are bitwise repeatable).
-__global__ __launch_bounds__(kCnnBlock) void k_wgrad_reduce(const float* part, int chunks, int cin, int cout,
-                                                            float* gw, float* gb) {
+__device__ __forceinline__ double chunk_sum(const float* part, int chunks, long stride, int p) {
     __shared__ double red[16][16];
     const int pl = threadIdx.x & 15, l = threadIdx.x >> 4;
-    const int p = blockIdx.x * 16 + pl;
     double s = 0.0;
     // chunks l, l + 16, ... in order, eight loads in flight
     int c = l;
     for (; c + 7 * 16 < chunks; c += 8 * 16) {
         float v[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = part[(long)(c + 16 * u) * 28 * 1024 + p];
+        for (int u = 0; u < 8; ++u) v[u] = part[(c + 16 * u) * stride + p];
 #pragma unroll
         for (int u = 0; u < 8; ++u) s += v[u];
     }
-    for (; c < chunks; c += 16) s += part[(long)c * 28 * 1024 + p];
+    for (; c < chunks; c += 16) s += part[c * stride + p];
     red[l][pl] = s;
     __syncthreads();
-    if (l == 0) {
-        double t = 0.0;
+    double t = 0.0;
+    if (l == 0)
         for (int k = 0; k < 16; ++k) t += red[k][pl];
+    return t;
+}
+
+__global__ __launch_bounds__(kCnnBlock) void k_wgrad_reduce(const float* part, int chunks, float* gw, float* gb) {
+    const int p = blockIdx.x * 16 + (threadIdx.x & 15);
+    const double t = chunk_sum(part, chunks, 28 * 1024, p);
+    if (threadIdx.x < 16) {
         const int ci = p & 31, co = (p >> 5) & 31, tap = p >> 10;
-        if (tap < 27) {
-            if (ci < cin && co < cout) gw[(tap * cin + ci) * cout + co] = (float)t;
-        } else if (ci == 0 && co < cout) {
-            gb[co] = (float)t;
+        if (tap < 27) gw[(tap * 32 + ci) * 32 + co] = (float)t;
+        else if (ci == 0) gb[co] = (float)t;
+    }
+}
+
+// Weight gradients of a layer with one channel on one side: D[t][c] = sum_u
+// X[u + s off(t)] Y[u][c] with the 27 taps as the MFMA's M dimension, the 32
+// channels of the other side as N and 16 voxels along x as K -- one product
+// per 16 voxels.  FIRST (x the layer input, y the output gradient): s = +1,
+// and row 27 of the A operand is ones, so D[27] is the bias gradient.  Else (x
+// the output gradient, y the layer input): s = -1, i.e. the taps read their
+// mirrored offsets, and the bias gradient sum_u x[u] is the centre tap's row
+// of a second product against ones.
+// A block walks a run of 16 x 32 tile-slices as the convolutions do.  X of a
+// slice (with halo, bf16) lies in a ring of four slots, three copies shifted
+// by the x offset so that every tap reads aligned 16-byte chunks; Y is
+// transposed on its way to LDS, channel-major.  Bound by reading Y once:
+// 24 x 32x64x64 voxels (201 MB) take 40 us, where the general kernel with
+// the one channel padded to 32 took 148 us.
+constexpr int kOneRow = 40;                              // bf16 per row of an X copy (32 + padding)
+constexpr int kOneCopy = kRingRows * kOneRow;
+constexpr int kOneSlot = 3 * kOneCopy;
+constexpr int kOnePlane = kTileRows * kTileCols + 8;     // bf16 per channel plane of Y
+static_assert(kOnePlane % 8 == 0 && kOneRow % 8 == 0 && kOneCopy % 8 == 0, "chunks stay 16-byte aligned");
+
+__device__ __forceinline__ void one_store_x(uint16_t* xs, int zi, const float (&pre)[kFirstFill]) {
+    uint16_t* slot = xs + ((zi + 4) & 3) * kOneSlot;
+#pragma unroll
+    for (int i = 0; i < kFirstFill; ++i) {
+        const int e = threadIdx.x + i * kCnnBlock;
+        const int c = e % kRingCols, r = e / kRingCols;
+        const uint16_t v = f2bf(pre[i]);
+        if (e < kFirstSlice) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+                if (c - d >= 0 && c - d < kTileCols) slot[d * kOneCopy + r * kOneRow + c - d] = v;
         }
+    }
+}
+
+template <bool FIRST>
+__global__ __launch_bounds__(kCnnBlock) void k_wgrad_one(ConvArgs a) {
+    __shared__ __attribute__((aligned(16))) uint16_t xs[4 * kOneSlot];
+    __shared__ __attribute__((aligned(16))) uint16_t yt[32 * kOnePlane];
+    static_assert(4 * 2 * 16 * 64 * sizeof(float) <= sizeof(yt), "the waves' sums fit in Y's planes");
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, m = lane & 31, h = lane >> 5;
+    // this lane's tap (row m of A), as ring slice offset and in-slot offset
+    const int tap = FIRST ? m : 26 - m;
+    const bool real = m < 27;
+    const int tz = real ? tap / 9 : 0, toff = real ? (tap % 3) * kOneCopy + (tap / 3 % 3) * kOneRow : 0;
+    const uint32_t fill = FIRST && m == 27 ? 0x3f803f80u : 0u;  // ones in the bias row
+    // this thread's 8 voxel x 8 channel unit of Y: channel group, row, chunk
+    const int cg = tid & 3, ch = (tid >> 2) & 3, yr = tid >> 4;
+    v8bf ones;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
+    v16f acc = {}, accb = {};
+
+    long t = (long)blockIdx.x * a.span;
+    const long total = (long)a.nvol * a.tiles_x * a.tiles_y * a.nz;
+    const long tend = t + a.span < total ? t + a.span : total;
+    ConvSeg sg;
+    while (next_seg(a, t, tend, sg)) {
+        const int x0 = sg.xt * kTileCols, y0 = sg.yt * kTileRows, z0 = sg.z0, z1 = sg.z1;
+        const long vol_off = (long)sg.vol * a.nz * a.ny * a.nx;
+        const float* xin = a.xin + vol_off;
+        const bool row_ok = y0 + yr < a.ny;
+        uint32_t yv[8][4];
+        auto fetch_y = [&](int z) {
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<uint16_t*>(a.in) + (vol_off + (long)z * a.ny * a.nx) * 32, 0,
+                (uint32_t)(a.ny * a.nx) * 64u, kBufferWord3);
+            const uint32_t off = (uint32_t)(((y0 + yr) * a.nx + x0 + 8 * ch) * 64 + 16 * cg);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const v4u q = __builtin_amdgcn_raw_buffer_load_b128(rs, row_ok ? off + 64 * e : kBufferOutside, 0,
+                                                                     kNonTemporal);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) yv[e][k] = q[k];
+            }
+        };
+        float px[kFirstFill];
+        {
+            float p0[kFirstFill], p1[kFirstFill];
+            first_fetch(a, xin, z0 - 1, y0, x0, p0, true);
+            first_fetch(a, xin, z0, y0, x0, p1, true);
+            first_fetch(a, xin, z0 + 1, y0, x0, px, true);
+            fetch_y(z0);
+            __syncthreads();  // the previous segment's readers are done
+            one_store_x(xs, z0 - 1, p0);
+            one_store_x(xs, z0, p1);
+        }
+        for (int z = z0; z < z1; ++z) {
+            if (z > z0) __syncthreads();  // the previous slice's readers are done
+            one_store_x(xs, z + 1, px);
+            uint32_t tr[8][4];
+            transpose8(yv, tr);
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                *reinterpret_cast<uint4*>(yt + (8 * cg + k) * kOnePlane + yr * kTileCols + 8 * ch) =
+                    make_uint4(tr[k][0], tr[k][1], tr[k][2], tr[k][3]);
+            if (z + 1 < z1) {
+                first_fetch(a, xin, z + 2, y0, x0, px, true);
+                fetch_y(z + 1);
+            }
+            __syncthreads();
+            const uint16_t* xl = xs + ((z + tz + 3) & 3) * kOneSlot + toff + 8 * h;
+            const uint16_t* yl = yt + m * kOnePlane + 8 * h;
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const int row = 4 * wave + r;
+                    uint4 q = *reinterpret_cast<const uint4*>(xl + row * kOneRow + 16 * k);
+                    q = real ? q : make_uint4(fill, fill, fill, fill);
+                    const v8bf A = __builtin_bit_cast(v8bf, q);
+                    const v8bf B = __builtin_bit_cast(
+                        v8bf, *reinterpret_cast<const uint4*>(yl + row * kTileCols + 16 * k));
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, B, acc, 0, 0, 0);
+                    if constexpr (!FIRST) accb = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, ones, accb, 0, 0, 0);
+                }
+        }
+    }
+    // the block's sums: the waves' in order, through LDS
+    float* red = reinterpret_cast<float*>(yt);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) red[(wave * 16 + i) * 64 + lane] = acc[i];
+    if constexpr (!FIRST) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) red[((4 + wave) * 16 + i) * 64 + lane] = accb[i];
+    }
+    __syncthreads();
+    float* dst = a.out_f32 + (long)blockIdx.x * 1024;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int i = 4 * j + wave, row = d_row(lane, i);
+        float s = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) s += red[(w * 16 + i) * 64 + lane];
+        if (FIRST || row != 27) dst[row * 32 + m] = s;
+        if constexpr (!FIRST) {
+            if (row == 13) {  // the centre tap reads x[u] itself
+                float sb = 0.f;
+#pragma unroll
+                for (int w = 0; w < 4; ++w) sb += red[((4 + w) * 16 + i) * 64 + lane];
+                dst[27 * 32 + m] = sb;
+            }
+        }
+    }
+}
+
+// Sum of k_wgrad_one's block sums: gw[t * 32 + c] and the bias gradient (32
+// values, or one for the output layer).
+__global__ __launch_bounds__(kCnnBlock) void k_wgrad_one_reduce(const float* part, int chunks, int first, float* gw,
+                                                                float* gb) {
+    const int p = blockIdx.x * 16 + (threadIdx.x & 15);
+    const double t = chunk_sum(part, chunks, 1024, p);
+    if (threadIdx.x < 16) {
+        if (p < 27 * 32) gw[p] = (float)t;
+        else if (first || p == 27 * 32) gb[p - 27 * 32] = (float)t;
     }
 }
 
@@ -1268,7 +1449,7 @@ static int grid_for(long work, int per_block, int cap) {
 // times the CU count; computed once per kernel), each with a contiguous run
 // of output tile-slices.
 template <void (*K)(ConvArgs), int NT = kCnnBlock>
-static hipError_t launch_conv(ConvArgs a, long total, hipStream_t st) {
+static hipError_t launch_conv(ConvArgs a, long total, hipStream_t st, int* blocks = nullptr) {
     static int cap = 0;
     if (cap == 0) {
         int per_cu = 0;
@@ -1278,6 +1459,7 @@ static hipError_t launch_conv(ConvArgs a, long total, hipStream_t st) {
     }
     a.span = (int)((total + cap - 1) / cap);
     const unsigned grid = (unsigned)((total + a.span - 1) / a.span);
+    if (blocks != nullptr) *blocks = (int)grid;
     hipLaunchKernelGGL(K, dim3(grid), dim3(NT), 0, st, a);
     return hipGetLastError();
 }
@@ -1285,7 +1467,7 @@ static hipError_t launch_conv(ConvArgs a, long total, hipStream_t st) {
 // Rows per wave of the 8- and 32-channel convolutions: two for the forward
 // layers, four for the backward-data ones.
 template <int EPI>
-constexpr int conv_rpw() { return EPI == EPI_RELU ? 2 : 4; }
+constexpr int conv_rpw() { return EPI == EPI_RELU || EPI == EPI_RELU_BITS ? 2 : 4; }
 
 // First-layer fragments (k_conv_first): wq[f][h][n][8] = W[t][n] with the
 // model tap t = 9 dz + j of K element (f, h, k8) -- f = 0: dz = h, j = k8;
@@ -1315,20 +1497,22 @@ hipError_t cnn_conv(int cin, int epi, ConvArgs a, hipStream_t st) {
     const long total = (long)a.nvol * a.tiles_x * a.tiles_y * a.nz;
     if (total <= 0) return hipSuccess;
     if (cin == 1 && epi == EPI_RELU) return launch_conv<k_conv_first>(a, total, st);
-#define CONV(C, E) launch_conv<k_conv<C, E, conv_rpw<E>()>, conv_threads<conv_rpw<E>()>()>(a, total, st)
-    if (cin == 8 && epi == EPI_RELU) return CONV(8, EPI_RELU);
-    if (cin == 32 && epi == EPI_RELU) return CONV(32, EPI_RELU);
     if (cin == 32 && epi == EPI_FINAL) return launch_conv<k_conv_final>(a, total, st);
-    if (cin == 8 && epi == EPI_DGRAD) return CONV(8, EPI_DGRAD);
-    if (cin == 32 && epi == EPI_DGRAD) return CONV(32, EPI_DGRAD);
-    if (cin == 8 && epi == EPI_RAW) return CONV(8, EPI_RAW);
-    if (cin == 32 && epi == EPI_RAW) return CONV(32, EPI_RAW);
+#define CONV(C, E)             \
+    if (cin == C && epi == E)  \
+    return launch_conv<k_conv<C, E, conv_rpw<E>()>, conv_threads<conv_rpw<E>()>()>(a, total, st)
+    CONV(8, EPI_RELU_BITS);
+    CONV(8, EPI_DGRAD);
+    CONV(8, EPI_RAW);
+    CONV(32, EPI_RELU);
+    CONV(32, EPI_RELU_BITS);
+    CONV(32, EPI_DGRAD);
+    CONV(32, EPI_RAW);
 #undef CONV
     return hipErrorInvalidValue;
 }
 
 size_t cnn_wq_elems(int cinp) { return (size_t)9 * (cinp == 32 ? 6 : 2) * 32 * 16; }
-
 
 hipError_t cnn_pack(const float* x, const float* scale, long nvox, uint16_t* x8, hipStream_t st) {
     hipLaunchKernelGGL(k_pack, dim3(grid_for(nvox, kCnnBlock, 8192)), dim3(kCnnBlock), 0, st, x, scale, nvox, x8);
@@ -1344,10 +1528,10 @@ hipError_t cnn_mean(const float* x, long nvox, double* part, float* mean, hipStr
     return hipGetLastError();
 }
 
-hipError_t cnn_loss(const float* out, const float* target, long nvox, uint16_t* g8, double* part, double* loss,
-                    hipStream_t st) {
+hipError_t cnn_loss(const float* out, const float* target, long nvox, uint16_t* g8, float* g1, double* part,
+                    double* loss, hipStream_t st) {
     const int nb = cnn_reduce_blocks(nvox);
-    hipLaunchKernelGGL(k_loss, dim3(nb), dim3(kCnnBlock), 0, st, out, target, nvox, g8, part);
+    hipLaunchKernelGGL(k_loss, dim3(nb), dim3(kCnnBlock), 0, st, out, target, nvox, g8, g1, part);
     hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(kCnnBlock), 0, st, part, nb, nvox, loss);
     return hipGetLastError();
 }
@@ -1365,7 +1549,7 @@ int cnn_wgrad_grid() {
 
 size_t cnn_wgrad_part_bytes() { return (size_t)cnn_wgrad_grid() * 28 * 1024 * sizeof(float); }
 
-hipError_t cnn_wgrad(int ca, int cg, WgradArgs a, int cin, int cout, float* gw, float* gb, hipStream_t st) {
+hipError_t cnn_wgrad(WgradArgs a, float* gw, float* gb, hipStream_t st) {
     a.tiles_x = a.nx / 32;
     a.tiles_y = (a.ny + kWgRows - 1) / kWgRows;
     const long tiles = (long)a.nvol * a.tiles_x * a.tiles_y;
@@ -1377,13 +1561,31 @@ hipError_t cnn_wgrad(int ca, int cg, WgradArgs a, int cin, int cout, float* gw, 
     if (items >= (1L << 31)) return hipErrorInvalidValue;
     a.items = (int)items;
     const int grid = (int)(items < grid_max ? items : grid_max);
-#define LAUNCH(A, G) hipLaunchKernelGGL((k_wgrad<A, G>), dim3(grid), dim3(kWgBlock), 0, st, a)
-    if (ca == 8 && cg == 32) LAUNCH(8, 32);
-    else if (ca == 32 && cg == 32) LAUNCH(32, 32);
-    else if (ca == 32 && cg == 8) LAUNCH(32, 8);
-    else return hipErrorInvalidValue;
-#undef LAUNCH
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3(28 * 1024 / 16), dim3(kCnnBlock), 0, st, a.part, grid, cin, cout, gw, gb);
+    hipLaunchKernelGGL(k_wgrad, dim3(grid), dim3(kWgBlock), 0, st, a);
+    hipLaunchKernelGGL(k_wgrad_reduce, dim3(28 * 1024 / 16), dim3(kCnnBlock), 0, st, a.part, grid, gw, gb);
+    return hipGetLastError();
+}
+
+hipError_t cnn_wgrad_one(int first, int nvol, int nz, int ny, int nx, const float* x, const uint16_t* y, float* part,
+                         float* gw, float* gb, hipStream_t st) {
+    // one slice of the 32-channel tensor must stay below the buffer offset that marks "outside"
+    if ((long)ny * nx * 64 >= (long)kBufferOutside) return hipErrorInvalidValue;
+    ConvArgs a{};
+    a.nvol = nvol;
+    a.nz = nz;
+    a.ny = ny;
+    a.nx = nx;
+    a.tiles_x = nx / kTileCols;
+    a.tiles_y = (ny + kTileRows - 1) / kTileRows;
+    a.xin = x;
+    a.in = y;
+    a.out_f32 = part;
+    const long total = (long)nvol * a.tiles_x * a.tiles_y * nz;
+    int grid = 0;
+    const hipError_t e = first ? launch_conv<k_wgrad_one<true>>(a, total, st, &grid)
+                               : launch_conv<k_wgrad_one<false>>(a, total, st, &grid);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_wgrad_one_reduce, dim3(28 * 32 / 16), dim3(kCnnBlock), 0, st, part, grid, first, gw, gb);
     return hipGetLastError();
 }
 

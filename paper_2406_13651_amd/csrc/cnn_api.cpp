@@ -54,7 +54,7 @@ clamp_status hip_check(hipError_t e, const char* what) {
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Layout {
-    size_t x8, act[kLayers], out, g8, ga, gb, mean, part, wpart, total;
+    size_t x8, act[kLayers], bits[kLayers], out, g8, g1, ga, gb, mean, part, wpart, total;
 };
 
 Layout layout(long nvox, bool train) {
@@ -68,8 +68,10 @@ Layout layout(long nvox, bool train) {
     if (train) L.x8 = take(nvox * 16);  // evaluation reads the fp32 input in the first layer
     if (train) {
         for (int l = 1; l < kLayers; ++l) L.act[l] = take(nvox * 64);
+        for (int l = 1; l < kLayers; ++l) L.bits[l] = take(nvox * 4);
         L.out = take(nvox * 4);
         L.g8 = take(nvox * 16);
+        L.g1 = take(nvox * 4);
         L.ga = take(nvox * 64);
         L.gb = take(nvox * 64);
         L.wpart = take(clampk::cnn_wgrad_part_bytes());
@@ -143,12 +145,12 @@ ConvArgs conv_args(int32_t nvol, int32_t nz, int32_t ny, int32_t nx) {
     return a;
 }
 
-// Forward pass; stores every activation when `acts` is non-null (training),
-// else ping-pongs between two buffers.  Training packs the input into the
-// 8-channel bf16 form (x8), which the first layer's weight gradient reads;
+// Forward pass; stores every activation and its ReLU pattern when `acts` is
+// non-null (training), else ping-pongs between two buffers.  Training packs the input into the
+// 8-channel bf16 form (x8);
 // evaluation runs the first layer straight from the fp32 volume.
 hipError_t forward(clamp_cnn* c, const float* x, float* out, const float* scale, int32_t nvol, int32_t nz,
-                   int32_t ny, int32_t nx, uint16_t* x8, uint16_t* const* acts, uint16_t* ping, uint16_t* pong,
+                   int32_t ny, int32_t nx, uint16_t* x8, uint16_t* const* acts, uint16_t* const* bits, uint16_t* ping, uint16_t* pong,
                    hipStream_t st) {
     const long nvox = (long)nvol * nz * ny * nx;
     const bool packed = acts != nullptr;
@@ -162,6 +164,7 @@ hipError_t forward(clamp_cnn* c, const float* x, float* out, const float* scale,
         if (l < kLayers - 1) {
             uint16_t* dst = acts ? acts[l + 1] : ((l % 2 == 0) ? ping : pong);
             a.out = dst;
+            if (acts) a.mask_out = bits[l + 1];
             if (l == 0 && !packed) {
                 a.in = nullptr;
                 a.xin = x;
@@ -169,7 +172,7 @@ hipError_t forward(clamp_cnn* c, const float* x, float* out, const float* scale,
                 a.wq = c->wq1;
                 e = clampk::cnn_conv(1, clampk::EPI_RELU, a, st);
             } else {
-                e = clampk::cnn_conv(cinp_of(l), clampk::EPI_RELU, a, st);
+                e = clampk::cnn_conv(cinp_of(l), acts ? clampk::EPI_RELU_BITS : clampk::EPI_RELU, a, st);
             }
             in = dst;
         } else {
@@ -272,7 +275,7 @@ clamp_status clamp_cnn_apply(clamp_cnn* cnn, const float* x, float* out, int32_t
         e = clampk::cnn_mean(x, nvox, at<double>(workspace, L.part), mean, s);
     }
     if (e == hipSuccess)
-        e = forward(cnn, x, out, mean, nvol, nz, ny, nx, nullptr, nullptr,
+        e = forward(cnn, x, out, mean, nvol, nz, ny, nx, nullptr, nullptr, nullptr,
                     at<uint16_t>(workspace, L.act[1]), at<uint16_t>(workspace, L.act[2]), s);
     return hip_check(e, "clamp_cnn_apply launch");
 }
@@ -287,31 +290,45 @@ clamp_status clamp_cnn_grad(clamp_cnn* cnn, const float* x, const float* target,
     const long nvox = (long)nvol * nz * ny * nx;
     const Layout L = layout(nvox, true);
     uint16_t* acts[kLayers];
-    acts[0] = at<uint16_t>(workspace, L.x8);
-    for (int l = 1; l < kLayers; ++l) acts[l] = at<uint16_t>(workspace, L.act[l]);
+    uint16_t* bits[kLayers];
+    for (int l = 1; l < kLayers; ++l) {
+        acts[l] = at<uint16_t>(workspace, L.act[l]);
+        bits[l] = at<uint16_t>(workspace, L.bits[l]);
+    }
     float* out = at<float>(workspace, L.out);
+    float* part = at<float>(workspace, L.wpart);
     float* g = grad != nullptr ? grad : cnn->grad;
-    hipError_t e = forward(cnn, x, out, nullptr, nvol, nz, ny, nx, acts[0], acts, nullptr, nullptr, s);
+    hipError_t e = forward(cnn, x, out, nullptr, nvol, nz, ny, nx, at<uint16_t>(workspace, L.x8), acts, bits, nullptr,
+                           nullptr, s);
     uint16_t* g8 = at<uint16_t>(workspace, L.g8);
-    if (e == hipSuccess) e = clampk::cnn_loss(out, target, nvox, g8, at<double>(workspace, L.part), loss, s);
+    float* g1 = at<float>(workspace, L.g1);
+    if (e == hipSuccess) e = clampk::cnn_loss(out, target, nvox, g8, g1, at<double>(workspace, L.part), loss, s);
     // backward: g holds dL/dz_l with channels coutp_of(l) (8 for the last layer)
     const uint16_t* gl = g8;
     uint16_t* gbuf[2] = {at<uint16_t>(workspace, L.ga), at<uint16_t>(workspace, L.gb)};
     for (int l = kLayers - 1; l >= 0 && e == hipSuccess; --l) {
-        WgradArgs wa{};
-        wa.nvol = nvol;
-        wa.nz = nz;
-        wa.ny = ny;
-        wa.nx = nx;
-        wa.act = acts[l];
-        wa.g = gl;
-        wa.part = at<float>(workspace, L.wpart);
-        e = clampk::cnn_wgrad(cinp_of(l), coutp_of(l), wa, cin_of(l), cout_of(l), g + w_offset(l), g + b_offset(l), s);
+        float* gw = g + w_offset(l);
+        float* gb = g + b_offset(l);
+        if (l == kLayers - 1) {
+            e = clampk::cnn_wgrad_one(0, nvol, nz, ny, nx, g1, acts[l], part, gw, gb, s);
+        } else if (l == 0) {
+            e = clampk::cnn_wgrad_one(1, nvol, nz, ny, nx, x, gl, part, gw, gb, s);
+        } else {
+            WgradArgs wa{};
+            wa.nvol = nvol;
+            wa.nz = nz;
+            wa.ny = ny;
+            wa.nx = nx;
+            wa.act = acts[l];
+            wa.g = gl;
+            wa.part = part;
+            e = clampk::cnn_wgrad(wa, gw, gb, s);
+        }
         if (e == hipSuccess && l > 0) {
             ConvArgs a = conv_args(nvol, nz, ny, nx);
             a.in = gl;
             a.wq = cnn->wqd[l];
-            a.relu_src = acts[l];
+            a.mask = bits[l];
             a.out = gbuf[l % 2];
             e = clampk::cnn_conv(coutp_of(l), clampk::EPI_DGRAD, a, s);
             gl = gbuf[l % 2];

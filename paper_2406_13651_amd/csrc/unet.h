@@ -61,9 +61,10 @@ size_t unet_chan_part_bytes();
 hipError_t unet_chan_finalize(int mode, const double* part, int blocks, long m, const float* gamma, const float* beta,
                               float* mean, float* rstd, float* A, float* B, float* C, float* run_mean,
                               float* run_var, float* out0, float* out1, hipStream_t st);
-// out = bf16([ReLU](A x + B y + C)) per channel (Y may be NULL: no B y term).
+// out = bf16([ReLU](A x + B y + C)) per channel (Y may be NULL: no B y term),
+// and with relu its ReLU pattern (cnn.h) into bits.
 hipError_t unet_affine(const uint16_t* X, const uint16_t* Y, const float* A, const float* B, const float* C, int relu,
-                       long nvox, uint16_t* out, hipStream_t st);
+                       long nvox, uint16_t* out, uint16_t* bits, hipStream_t st);
 // de = [e > 0] (dp routed to each window's first maximum + dskip) (fine sizes).
 hipError_t unet_pool_bwd(const uint16_t* e, const uint16_t* dp, const uint16_t* dskip, uint16_t* de, int nvol, int nz,
                          int ny, int nx, hipStream_t st);

@@ -345,10 +345,12 @@ __global__ __launch_bounds__(1024) void k_chan_finalize(int mode, const double* 
 }
 
 // out = bf16([ReLU](A x + B y + C)) per channel over a bf16 [nvox][32] tensor
-// (y only when HAS_Y).
+// (y only when HAS_Y).  With RELU the pattern of positive outputs goes to
+// bits: this thread's channels 8 j .. 8 j + 7 are byte j / 2 of word j % 2.
 template <bool HAS_Y, bool RELU>
 __global__ __launch_bounds__(kBlock) void k_affine(const uint16_t* X, const uint16_t* Y, const float* A,
-                                                   const float* B, const float* Cc, long nvox, uint16_t* out) {
+                                                   const float* B, const float* Cc, long nvox, uint16_t* out,
+                                                   uint8_t* bits) {
     const long n = nvox * 4;
     // the grid stride is a multiple of 4, so each thread keeps one channel group
     const int j = (int)(threadIdx.x & 3);
@@ -369,7 +371,16 @@ __global__ __launch_bounds__(kBlock) void k_affine(const uint16_t* X, const uint
             if constexpr (HAS_Y) v += b8[c] * y[c];
             o[c] = RELU ? fmaxf(v, 0.f) : v;
         }
-        *reinterpret_cast<uint4*>(out + i * 8) = pack8(o);
+        const uint4 q = pack8(o);
+        *reinterpret_cast<uint4*>(out + i * 8) = q;
+        if constexpr (RELU) {
+            const uint32_t d[4] = {q.x, q.y, q.z, q.w};
+            uint32_t b = 0u;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                b |= ((d[k] & 0x7fffu) != 0u ? 1u : 0u) << (2 * k) | ((d[k] & 0x7fff0000u) != 0u ? 2u : 0u) << (2 * k);
+            bits[(i >> 2) * 4 + (j & 1) * 2 + (j >> 1)] = (uint8_t)b;
+        }
     }
 }
 
@@ -681,12 +692,13 @@ hipError_t unet_chan_finalize(int mode, const double* part, int blocks, long m, 
 }
 
 hipError_t unet_affine(const uint16_t* X, const uint16_t* Y, const float* A, const float* B, const float* C, int relu,
-                       long nvox, uint16_t* out, hipStream_t st) {
+                       long nvox, uint16_t* out, uint16_t* bits, hipStream_t st) {
     const dim3 g(grid_of(nvox * 4, 1 << 20)), b(kBlock);
-    if (Y != nullptr && relu) hipLaunchKernelGGL((k_affine<true, true>), g, b, 0, st, X, Y, A, B, C, nvox, out);
-    else if (Y != nullptr) hipLaunchKernelGGL((k_affine<true, false>), g, b, 0, st, X, Y, A, B, C, nvox, out);
-    else if (relu) hipLaunchKernelGGL((k_affine<false, true>), g, b, 0, st, X, Y, A, B, C, nvox, out);
-    else hipLaunchKernelGGL((k_affine<false, false>), g, b, 0, st, X, Y, A, B, C, nvox, out);
+    uint8_t* bb = reinterpret_cast<uint8_t*>(bits);
+    if (Y != nullptr && relu) hipLaunchKernelGGL((k_affine<true, true>), g, b, 0, st, X, Y, A, B, C, nvox, out, bb);
+    else if (Y != nullptr) hipLaunchKernelGGL((k_affine<true, false>), g, b, 0, st, X, Y, A, B, C, nvox, out, bb);
+    else if (relu) hipLaunchKernelGGL((k_affine<false, true>), g, b, 0, st, X, Y, A, B, C, nvox, out, bb);
+    else hipLaunchKernelGGL((k_affine<false, false>), g, b, 0, st, X, Y, A, B, C, nvox, out, bb);
     return hipGetLastError();
 }
 

@@ -270,7 +270,7 @@ int level_of(int l) { return l < 2 * kLevels ? l / 2 : (4 * kLevels - 1 - l) / 2
 
 // Workspace of a training step: every tensor the backward pass reads.
 struct TrainLayout {
-    size_t x8, out, g8, z[kConvs], a[kConvs], p[kLevels + 1], s[kLevels], gs[kLevels], G[kLevels][3], gp3;
+    size_t x8, out, g8, g1, z[kConvs], a[kConvs], bits[kConvs], p[kLevels + 1], s[kLevels], gs[kLevels], G[kLevels][3], gp3;
     size_t bn, coef, chanpart, uppart, wpart, part, total;
 };
 
@@ -287,9 +287,11 @@ TrainLayout train_layout(long nvox) {
     L.x8 = take(nvox * 16);
     L.out = take(nvox * 4);
     L.g8 = take(nvox * 16);
+    L.g1 = take(nvox * 4);
     for (int l = 0; l < kConvs; ++l) {
         L.z[l] = take(nv[level_of(l)] * 64);
         L.a[l] = take(nv[level_of(l)] * 64);
+        L.bits[l] = take(nv[level_of(l)] * 4);
     }
     for (int k = 1; k <= kLevels; ++k) L.p[k] = take(nv[k] * 64);
     for (int k = 0; k < kLevels; ++k) {
@@ -314,7 +316,8 @@ struct Trainer {
     const TrainLayout& L;
     int32_t nvol;
     int dz[kLevels + 1], dy[kLevels + 1], dx[kLevels + 1];
-    float* g;  // gradient vector
+    const float* x;  // the input volumes
+    float* g;        // gradient vector
     hipStream_t st;
 
     template <typename T>
@@ -327,7 +330,8 @@ struct Trainer {
         return a;
     }
 
-    // z = W * in (no bias), batch statistics, a = ReLU(BN(z)); updates the running statistics
+    // z = W * in (no bias), batch statistics, a = ReLU(BN(z)) with its ReLU
+    // pattern; updates the running statistics
     hipError_t conv_bn(int l, const uint16_t* in) {
         const int k = level_of(l);
         ConvArgs a = conv(k);
@@ -344,15 +348,16 @@ struct Trainer {
                                            bn(l, 0), bn(l, 1), bn(l, 2), bn(l, 3), nullptr, rmean, rmean + kWidth,
                                            nullptr, nullptr, st);
         if (e == hipSuccess)
-            e = clampk::unet_affine(a.out, nullptr, bn(l, 2), nullptr, bn(l, 3), 1, nvox(k), buf<uint16_t>(L.a[l]), st);
+            e = clampk::unet_affine(a.out, nullptr, bn(l, 2), nullptr, bn(l, 3), 1, nvox(k), buf<uint16_t>(L.a[l]),
+                                    buf<uint16_t>(L.bits[l]), st);
         return e;
     }
 
     // Backward of batch normalisation and convolution l: gy (gradient at the
     // ReLU output, already masked) -> dz -> weight, gamma and beta gradients;
-    // the input gradient into gin (masked by relu_src, or raw when NULL; not
-    // formed when gin is NULL).
-    hipError_t conv_bn_back(int l, const uint16_t* gy, uint16_t* dzb, const uint16_t* in, const uint16_t* relu_src,
+    // the input gradient into gin (masked by the ReLU pattern `mask`, or raw
+    // when NULL; not formed when gin is NULL).
+    hipError_t conv_bn_back(int l, const uint16_t* gy, uint16_t* dzb, const uint16_t* in, const uint16_t* mask,
                             uint16_t* gin) {
         const int k = level_of(l);
         int blocks = 0;
@@ -364,8 +369,11 @@ struct Trainer {
             e = clampk::unet_chan_finalize(1, part, blocks, nvox(k), u->params + conv_gamma(l), nullptr, bn(l, 0),
                                            bn(l, 1), c, c + 32, c + 64, nullptr, nullptr, g + conv_gamma(l),
                                            g + conv_beta(l), st);
-        if (e == hipSuccess) e = clampk::unet_affine(gy, z, c, c + 32, c + 64, 0, nvox(k), dzb, st);
-        if (e == hipSuccess) {
+        if (e == hipSuccess) e = clampk::unet_affine(gy, z, c, c + 32, c + 64, 0, nvox(k), dzb, nullptr, st);
+        if (e == hipSuccess && l == 0) {
+            e = clampk::cnn_wgrad_one(1, nvol, dz[0], dy[0], dx[0], x, dzb, buf<float>(L.wpart), g + conv_w(0),
+                                      u->bscratch, st);
+        } else if (e == hipSuccess) {
             clampk::WgradArgs wa{};
             wa.nvol = nvol;
             wa.nz = dz[k];
@@ -374,15 +382,15 @@ struct Trainer {
             wa.act = in;
             wa.g = dzb;
             wa.part = buf<float>(L.wpart);
-            e = clampk::cnn_wgrad(cinp_of(l), kWidth, wa, cin_of(l), kWidth, g + conv_w(l), u->bscratch, st);
+            e = clampk::cnn_wgrad(wa, g + conv_w(l), u->bscratch, st);
         }
         if (e == hipSuccess && gin != nullptr) {
             ConvArgs a = conv(k);
             a.in = dzb;
             a.wq = u->wqd[l];
-            a.relu_src = relu_src;
+            a.mask = mask;
             a.out = gin;
-            e = clampk::cnn_conv(kWidth, relu_src ? clampk::EPI_DGRAD : clampk::EPI_RAW, a, st);
+            e = clampk::cnn_conv(kWidth, mask ? clampk::EPI_DGRAD : clampk::EPI_RAW, a, st);
         }
         return e;
     }
@@ -390,7 +398,7 @@ struct Trainer {
 
 hipError_t train_step(clamp_unet* u, const float* x, const float* target, int32_t nvol, int32_t nz, int32_t ny,
                       int32_t nx, double* loss, float* g, void* ws, const TrainLayout& L, hipStream_t st) {
-    Trainer T{u, ws, L, nvol, {}, {}, {}, g, st};
+    Trainer T{u, ws, L, nvol, {}, {}, {}, x, g, st};
     for (int k = 0; k <= kLevels; ++k) {
         T.dz[k] = nz >> k;
         T.dy[k] = ny >> k;
@@ -437,26 +445,18 @@ hipError_t train_step(clamp_unet* u, const float* x, const float* target, int32_
         e = clampk::cnn_conv(kWidth, clampk::EPI_FINAL, a, st);
     }
     uint16_t* g8 = B(L.g8);
-    if (e == hipSuccess) e = clampk::cnn_loss(out, target, nvox, g8, T.buf<double>(L.part), loss, st);
+    float* g1 = T.buf<float>(L.g1);
+    if (e == hipSuccess) e = clampk::cnn_loss(out, target, nvox, g8, g1, T.buf<double>(L.part), loss, st);
     // backward: final layer
-    const uint16_t* d1 = B(L.a[4 * kLevels - 1]);
-    if (e == hipSuccess) {
-        clampk::WgradArgs wa{};
-        wa.nvol = nvol;
-        wa.nz = nz;
-        wa.ny = ny;
-        wa.nx = nx;
-        wa.act = d1;
-        wa.g = g8;
-        wa.part = T.buf<float>(L.wpart);
-        e = clampk::cnn_wgrad(kWidth, 8, wa, kWidth, 1, g + final_w(), g + final_b(), st);
-    }
+    if (e == hipSuccess)
+        e = clampk::cnn_wgrad_one(0, nvol, nz, ny, nx, g1, B(L.a[kConvs - 1]), T.buf<float>(L.wpart), g + final_w(),
+                                  g + final_b(), st);
     uint16_t* gcur = B(L.G[0][0]);
     if (e == hipSuccess) {
         ConvArgs a = T.conv(0);
         a.in = g8;
         a.wq = u->wqd[kConvs];
-        a.relu_src = d1;
+        a.mask = B(L.bits[kConvs - 1]);
         a.out = gcur;
         e = clampk::cnn_conv(8, clampk::EPI_DGRAD, a, st);
     }
@@ -467,7 +467,7 @@ hipError_t train_step(clamp_unet* u, const float* x, const float* target, int32_
         const int k = kLevels - 1 - j, l1 = 2 * kLevels + 2 * j, l2 = l1 + 1;
         uint16_t* G1 = B(L.G[k][1]);
         uint16_t* G2 = B(L.G[k][2]);
-        e = T.conv_bn_back(l2, gcur, G1, B(L.a[l1]), B(L.a[l1]), G2);
+        e = T.conv_bn_back(l2, gcur, G1, B(L.a[l1]), B(L.bits[l1]), G2);
         if (e == hipSuccess) e = T.conv_bn_back(l1, G2, G1, B(L.s[k]), nullptr, B(L.gs[k]));
         const uint16_t* xin = j == 0 ? B(L.p[kLevels]) : B(L.a[l1 - 1]);
         clampk::UpBwdArgs ub{};
@@ -498,7 +498,7 @@ hipError_t train_step(clamp_unet* u, const float* x, const float* target, int32_
         uint16_t* G1 = B(L.G[k][1]);
         uint16_t* G2 = B(L.G[k][2]);
         e = clampk::unet_pool_bwd(B(L.a[2 * k + 1]), gcur, B(L.gs[k]), G0, nvol, T.dz[k], T.dy[k], T.dx[k], st);
-        if (e == hipSuccess) e = T.conv_bn_back(2 * k + 1, G0, G1, B(L.a[2 * k]), B(L.a[2 * k]), G2);
+        if (e == hipSuccess) e = T.conv_bn_back(2 * k + 1, G0, G1, B(L.a[2 * k]), B(L.bits[2 * k]), G2);
         const uint16_t* in0 = k == 0 ? B(L.x8) : B(L.p[k]);
         if (e == hipSuccess) e = T.conv_bn_back(2 * k, G2, G1, in0, nullptr, k == 0 ? nullptr : G0);
         gcur = G0;
