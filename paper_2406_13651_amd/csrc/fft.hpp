@@ -23,6 +23,16 @@ __device__ __forceinline__ float2 cmul(float2 a, float2 b) {
 }
 __device__ __forceinline__ float cabs2(float2 a) { return a.x * a.x + a.y * a.y; }
 
+// a times the twiddle w (its conjugate for S > 0) with the rounding the compiler
+// gives cmul in fft_stages: the products with w.x inside the fused
+// multiply-adds.  Written out where neighbouring butterflies would otherwise
+// be combined into vector code of another rounding.
+template <int S>
+__device__ __forceinline__ float2 cmul_tw(float2 a, float2 w) {
+    if constexpr (S > 0) w.y = -w.y;
+    return make_float2(fmaf(a.x, w.x, -(a.y * w.y)), fmaf(a.y, w.x, a.x * w.y));
+}
+
 // a * (S i), S = +1 or -1
 template <int S>
 __device__ __forceinline__ float2 mul_si(float2 a) {
@@ -277,6 +287,111 @@ template <int N, int T, int S, int PADSH, bool IN_REGS, bool OUT_REGS, bool WAVE
 __device__ __forceinline__ void fft_regs(float2 (&h)[N / T], float2* buf, int stride, int t, const float2* tw) {
     fft_regs_at<N, T, S, IN_REGS, OUT_REGS, WAVE>(
         h, buf, [stride](int i) { return lds_pos<PADSH>(i) * stride; }, t, tw);
+}
+
+// Transforms of lengths outside fft_regs_ok whose last stages stay in
+// registers.  Stage s reads the elements j + r N / R and writes k + r NS +
+// (multiples of NS R), so where T divides both N / R and NS, a thread that
+// holds the elements t + k T finds its inputs among them and its outputs are
+// again elements t + k T: no exchange before or after the stage (384 points
+// on 64 threads: the radix-2 and radix-3 stages; 192 on 32: the radix-3
+// stage).  fft_tail is the first such stage after which all are.
+__host__ __device__ constexpr int fft_ns(int n, int s) {
+    int ns = 1;
+    for (int i = 0; i < s; ++i) ns *= radix_at(n, i);
+    return ns;
+}
+template <int N, int T>
+__host__ __device__ constexpr int fft_tail() {
+    int s = num_stages(N);
+    while (s > 0 && fft_ns(N, s - 1) % T == 0 && (N / radix_at(N, s - 1)) % T == 0) --s;
+    return s;
+}
+
+template <int N, int T, int S, int STAGE>
+__device__ __forceinline__ void fft_tail_stages(float2 (&h)[N / T], int t, const float2* tw) {
+    if constexpr (STAGE < num_stages(N)) {
+        constexpr int R = radix_at(N, STAGE);
+        constexpr int NS = fft_ns(N, STAGE);
+        constexpr int PER = N / R / T;
+        constexpr int TWSTEP = N / (NS * R);
+        float2 o[N / T];
+#pragma unroll
+        for (int p = 0; p < PER; ++p) {
+            float2 v[R];
+            const int k = t + (p * T) % NS;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                v[r] = h[p + r * PER];
+                if (r > 0) v[r] = cmul_tw<S>(v[r], tw[r * k * TWSTEP]);
+            }
+            Bfly<R, S>::run(v);
+#pragma unroll
+            for (int r = 0; r < R; ++r) o[((p * T) / NS * NS * R + (p * T) % NS + r * NS) / T] = v[r];
+        }
+#pragma unroll
+        for (int k = 0; k < N / T; ++k) h[k] = o[k];
+        fft_tail_stages<N, T, S, STAGE + 1>(h, t, tw);
+    }
+}
+
+// Stages STAGE .. END - 1 of fft_stages.
+template <int N, int T, int S, int PADSH, int STAGE, int END, bool WAVE>
+__device__ __forceinline__ void fft_head_stages(float2* buf, int t, const float2* tw) {
+    if constexpr (STAGE < END) {
+        constexpr int R = radix_at(N, STAGE);
+        constexpr int NS = fft_ns(N, STAGE);
+        constexpr int NB = N / R;
+        constexpr int TWSTEP = N / (NS * R);
+        static_assert(NB <= T, "one butterfly per thread");
+        float2 v[R];
+        if (t < NB) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[r] = buf[lds_pos<PADSH>(t + r * NB)];
+        }
+        group_sync<WAVE>();
+        if (t < NB) {
+            const int k = t % NS;
+#pragma unroll
+            for (int r = 1; r < R; ++r) v[r] = cmul_tw<S>(v[r], tw[r * k * TWSTEP]);
+            Bfly<R, S>::run(v);
+            const int base = (t / NS) * NS * R + k;
+#pragma unroll
+            for (int r = 0; r < R; ++r) buf[lds_pos<PADSH>(base + r * NS)] = v[r];
+        }
+        group_sync<WAVE>();
+        fft_head_stages<N, T, S, PADSH, STAGE + 1, END, WAVE>(buf, t, tw);
+    }
+}
+
+// Unnormalised length-N DFT from the first stage's inputs: v[r] = element t +
+// r N / R0 of the vector on the threads t < N / R0 (the others' are not
+// used).  The result goes to h (h[k] = element t + k T) and, unless OUT_REGS,
+// from there to buf in natural order, visible to the group.  Starts with a
+// group synchronisation, so earlier reads and writes of buf are done.
+template <int N, int T, int S, int PADSH, bool OUT_REGS, bool WAVE>
+__device__ __forceinline__ void fft_split(float2 (&v)[radix_at(N, 0)], float2 (&h)[N / T], float2* buf, int t,
+                                          const float2* tw) {
+    constexpr int R = radix_at(N, 0);
+    constexpr int TAIL = fft_tail<N, T>();
+    static_assert(N % T == 0 && N / R <= T && TAIL > 0 && TAIL < num_stages(N), "length and group size");
+    group_sync<WAVE>();
+    if (t < N / R) {
+        Bfly<R, S>::run(v);
+#pragma unroll
+        for (int r = 0; r < R; ++r) buf[lds_pos<PADSH>(t * R + r)] = v[r];
+    }
+    group_sync<WAVE>();
+    fft_head_stages<N, T, S, PADSH, 1, TAIL, WAVE>(buf, t, tw);
+#pragma unroll
+    for (int k = 0; k < N / T; ++k) h[k] = buf[lds_pos<PADSH>(t + k * T)];
+    fft_tail_stages<N, T, S, TAIL>(h, t, tw);
+    if constexpr (!OUT_REGS) {
+        group_sync<WAVE>();
+#pragma unroll
+        for (int k = 0; k < N / T; ++k) buf[lds_pos<PADSH>(t + k * T)] = h[k];
+        group_sync<WAVE>();
+    }
 }
 
 }  // namespace clampk

@@ -241,28 +241,56 @@ struct RowLds {
     float2* buf;
 };
 
-// Row transform of h (h[k] = element t + k TR of the row): in registers where
-// fft_regs applies (power-of-two rows), else through rb with fft_lds.  With
-// OUT_REGS the result returns to h; otherwise it is left in rb in natural
-// order, for gathers across the row by the row's own wave.
-template <int NX, int TR, int S, int PAD, bool OUT_REGS, int PX>
-__device__ __forceinline__ void row_fft(float2 (&h)[PX], float2* rb, int t, const float2* tw) {
-    if constexpr (NX % TR == 0 && fft_regs_ok<NX, TR>()) {
-        fft_regs<NX, TR, S, PAD, true, OUT_REGS, true>(h, rb, 1, t, tw);
+// How a row's first transform takes its samples: sample q of thread t is
+// element t + q kStep.  Power-of-two rows go through fft_regs, whose first
+// stage reads what the pointwise steps hold (t + k TR); 192- and 384-point rows
+// through fft_split, whose first stage is one radix-8 butterfly on each of
+// the threads t < kStep (384x192x37, 5 looks, against every stage through LDS:
+// gradient pass 85 -> 70 us, update pass 118 -> 98 us).
+template <int NX>
+struct RowIn {
+    static constexpr int TR = row_threads(NX);
+    static constexpr int PX = NX / TR;  // row samples per thread
+    static_assert(NX % TR == 0, "row samples divide among the threads");
+    static constexpr bool kRegs = fft_regs_ok<NX, TR>();
+    static constexpr int kStep = kRegs ? TR : NX / radix_at(NX, 0);
+    static constexpr int kCount = kRegs ? PX : radix_at(NX, 0);
+    __device__ __forceinline__ static bool has(int t) { return kRegs || t < kStep; }
+};
+
+// Row transform of in (the samples of RowIn) into h (h[k] = element t + k TR)
+// or, without OUT_REGS, into rb in natural order, for gathers across the row
+// by the row's own wave.
+template <int NX, int S, bool OUT_REGS>
+__device__ __forceinline__ void row_fft_in(float2 (&in)[RowIn<NX>::kCount], float2 (&h)[RowIn<NX>::PX], float2* rb,
+                                           int t, const float2* tw) {
+    using R = RowIn<NX>;
+    if constexpr (R::kRegs) {
+#pragma unroll
+        for (int k = 0; k < R::PX; ++k) h[k] = in[k];
+        fft_regs<NX, R::TR, S, kRowPad, true, OUT_REGS, true>(h, rb, 1, t, tw);
     } else {
+        fft_split<NX, R::TR, S, kRowPad, OUT_REGS, true>(in, h, rb, t, tw);
+    }
+}
+
+// Row transform of h (h[k] = element t + k TR of the row), to h or rb as above.
+template <int NX, int S, bool OUT_REGS>
+__device__ __forceinline__ void row_fft(float2 (&h)[RowIn<NX>::PX], float2* rb, int t, const float2* tw) {
+    using R = RowIn<NX>;
+    if constexpr (R::kRegs) {
+        fft_regs<NX, R::TR, S, kRowPad, true, OUT_REGS, true>(h, rb, 1, t, tw);
+    } else {
+        group_sync<true>();
 #pragma unroll
-        for (int k = 0; k < PX; ++k) {
-            const int x = t + k * TR;
-            if (NX % TR == 0 || x < NX) rb[lds_pos<PAD>(x)] = h[k];
-        }
-        fft_lds<NX, TR, S, PAD, true>(rb, 1, t, tw);
-        if constexpr (OUT_REGS) {
+        for (int k = 0; k < R::PX; ++k) rb[lds_pos<kRowPad>(t + k * R::TR)] = h[k];
+        group_sync<true>();
+        float2 in[R::kCount];
+        if (R::has(t)) {
 #pragma unroll
-            for (int k = 0; k < PX; ++k) {
-                const int x = t + k * TR;
-                if (NX % TR == 0 || x < NX) h[k] = rb[lds_pos<PAD>(x)];
-            }
+            for (int q = 0; q < R::kCount; ++q) in[q] = rb[lds_pos<kRowPad>(t + q * R::kStep)];
         }
+        fft_split<NX, R::TR, S, kRowPad, OUT_REGS, true>(in, h, rb, t, tw);
     }
 }
 
@@ -360,58 +388,55 @@ __device__ __forceinline__ void row_item(const A& a, int look, int rgroup, size_
     }
     float2* rb = L.buf + ri * RS;
 
-    // the row in registers: h[k] = element t + k TR (zero for inactive rows)
-    float2 h[PX];
+    // the row's samples for the first transform (zero for inactive rows), and
+    // the row in registers: h[k] = element t + k TR
+    using In = RowIn<NX>;
+    float2 in[In::kCount], h[PX];
+    const bool has = active && In::has(t);
     if constexpr (MODE == ROW_FWD) {
 #pragma unroll
-        for (int k = 0; k < PX; ++k) {
-            const int x = t + k * TR;
-            h[k] = (active && (NX % TR == 0 || x < NX)) ? a.img_in[img + x] : make_float2(0.f, 0.f);
-        }
+        for (int q = 0; q < In::kCount; ++q)
+            in[q] = has ? a.img_in[img + t + q * In::kStep] : make_float2(0.f, 0.f);
     } else {
-        // The row's band samples: all PX loads are issued before the first
+        // The row's band samples: all loads are issued before the first
         // is used (samples off the band read the row's first band sample and
         // are replaced by zero), then the pointwise streams are prefetched
         // behind them.
-        float2 bin[PX];
-        int bp[PX];
+        float2 bin[In::kCount];
+        int bp[In::kCount];
 #pragma unroll
-        for (int k = 0; k < PX; ++k) {
-            const int x = t + k * TR;
-            bp[k] = (active && (NX % TR == 0 || x < NX)) ? L.bpos[x] : -1;
-            bin[k] = ld_stream(a.band_in + band + (bp[k] >= 0 ? bp[k] : 0));  // inactive rows read row 0
+        for (int q = 0; q < In::kCount; ++q) {
+            bp[q] = has ? L.bpos[t + q * In::kStep] : -1;
+            bin[q] = ld_stream(a.band_in + band + (bp[q] >= 0 ? bp[q] : 0));  // inactive rows read row 0
         }
         if constexpr (PREFETCH) load_streams();
 #pragma unroll
-        for (int k = 0; k < PX; ++k) h[k] = bp[k] >= 0 ? bin[k] : make_float2(0.f, 0.f);
+        for (int q = 0; q < In::kCount; ++q) in[q] = bp[q] >= 0 ? bin[q] : make_float2(0.f, 0.f);
     }
 
     if constexpr (MODE == ROW_INV) {
-        row_fft<NX, TR, +1, PAD, true>(h, rb, t, L.tw);
+        row_fft_in<NX, +1, true>(in, h, rb, t, L.tw);
         if (active) {
 #pragma unroll
-            for (int k = 0; k < PX; ++k) {
-                const int x = t + k * TR;
-                if (NX % TR == 0 || x < NX) a.img_out[img + x] = cscale(h[k], a.scale);
-            }
+            for (int k = 0; k < PX; ++k) a.img_out[img + t + k * TR] = cscale(h[k], a.scale);
         }
     } else if constexpr (MODE == ROW_FWD) {
-        row_fft<NX, TR, -1, PAD, false>(h, rb, t, L.tw);
+        row_fft_in<NX, -1, false>(in, h, rb, t, L.tw);
         if (active)
             for (int b = t; b < s.B; b += TR)
                 a.band_out[band + band_col_off(b, s.ny)] = cscale(rb[lds_pos<PAD>(L.bcol[b])], a.scale);
     } else if constexpr (MODE == ROW_GRAD) {
-        row_fft<NX, TR, +1, PAD, true>(h, rb, t, L.tw);
+        row_fft_in<NX, +1, true>(in, h, rb, t, L.tw);
         float dd = 0.f, wd = 0.f, wm = 0.f;
         if (active) row_grad_pointwise<NX, TR>(a, h, t, m, rp, dd, wd, wm);
-        row_fft<NX, TR, -1, PAD, false>(h, rb, t, L.tw);
+        row_fft<NX, -1, false>(h, rb, t, L.tw);
         if (active)
             for (int b = t; b < s.B; b += TR)
                 st_stream(a.band_out + band + band_col_off(b, s.ny), cscale(rb[lds_pos<PAD>(L.bcol[b])], a.scale));
         double acc[3] = {dd, wd, wm};
         block_sum_store<3>(acc, a.part + slot * 3);
     } else {  // ROW_UPDATE
-        row_fft<NX, TR, +1, PAD, true>(h, rb, t, L.tw);
+        row_fft_in<NX, +1, true>(in, h, rb, t, L.tw);
         if constexpr (!PREFETCH) load_streams();
         const float gamma = (float)a.diag[(size_t)look * kDiag];
         float wm1 = 0.f;
@@ -539,20 +564,21 @@ __device__ __forceinline__ void row_update_mann(const A& a, const F& f, int spli
         if (l < a.looks) {
             const size_t img = (size_t)l * n + pix;
             const size_t band = ((size_t)l * s.nz + arow / s.ny) * s.ny * s.Bs + band_row_off(arow % s.ny, s.ny);
-            float2 h[PX];
+            using In = RowIn<NX>;
+            float2 in[In::kCount], h[PX];
             {
-                float2 bin[PX];
-                int bp[PX];
+                const bool has = active && In::has(t);
+                float2 bin[In::kCount];
+                int bp[In::kCount];
 #pragma unroll
-                for (int k = 0; k < PX; ++k) {
-                    const int x = t + k * TR;
-                    bp[k] = (active && (NX % TR == 0 || x < NX)) ? L.bpos[x] : -1;
-                    bin[k] = ld_stream(a.band_in + band + (bp[k] >= 0 ? bp[k] : 0));
+                for (int q = 0; q < In::kCount; ++q) {
+                    bp[q] = has ? L.bpos[t + q * In::kStep] : -1;
+                    bin[q] = ld_stream(a.band_in + band + (bp[q] >= 0 ? bp[q] : 0));
                 }
 #pragma unroll
-                for (int k = 0; k < PX; ++k) h[k] = bp[k] >= 0 ? bin[k] : make_float2(0.f, 0.f);
+                for (int q = 0; q < In::kCount; ++q) in[q] = bp[q] >= 0 ? bin[q] : make_float2(0.f, 0.f);
             }
-            row_fft<NX, TR, +1, PAD, true>(h, rb, t, L.tw);
+            row_fft_in<NX, +1, true>(in, h, rb, t, L.tw);
             float2 m[PX];
             float rp[PX], uv[PX];
             if (active) {
@@ -1044,14 +1070,14 @@ __device__ __forceinline__ void slice_grad_item(const A& a, int zl, float2* lds)
             h[k] = b >= 0 ? srow[b] : make_float2(0.f, 0.f);
             if (b >= 0) st_stream(brow + band_col_off(b, NY), h[k]);
         }
-        row_fft<NX, TR, +1, kRowPad, true>(h, rb, t, twx);
+        row_fft<NX, +1, true>(h, rb, t, twx);
         float dd = 0.f, wd = 0.f, wm = 0.f;
         row_grad_pointwise<NX, TR, true>(a, h, t, m, rp, dd, wd, wm);
         acc[0] += dd;
         acc[1] += wd;
         acc[2] += wm;
         if (y0 + NW * RPW < NY) load_streams(y + NW * RPW);
-        row_fft<NX, TR, -1, kRowPad, false>(h, rb, t, twx);
+        row_fft<NX, -1, false>(h, rb, t, twx);
         for (int b = t; b < B; b += TR) srow[b] = cscale(rb[lds_pos<kRowPad>(bcol[b])], a.scale);
     }
     __syncthreads();

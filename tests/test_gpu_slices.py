@@ -3,7 +3,8 @@ of their tilings: the one-launch passes of a slice (32- and 64-point
 transforms, equal and unequal lengths, pupils from three band columns to the
 whole row, one slice, odd slice counts, the 3D operator), and the fused
 update pass with one, two or four waves sharing a row group's looks (look
-counts that the sharing does not divide).  The forward agents alone and with
+counts that the sharing does not divide), and the 192- and 384-point rows of
+the split transform.  The forward agents alone and with
 the Mann step fused in.
 
 Bound: each iteration's arrays carry a few float32 roundings of the FFTs and
@@ -35,6 +36,9 @@ CASES = [
     (128, 64, 3, 4, 16.0, True, 0),    # four waves, three-pass gradient
     (256, 32, 2, 3, 8.0, True, 0),
     (192, 32, 2, 6, 8.0, True, 0),     # rows that do not fill their threads
+    (192, 64, 3, 4, 101.5, True, 0),   # the same with every sample of a row in the band
+    (384, 32, 3, 5, 193.0, True, 0),
+    (384, 64, 5, 1, 2.0, False, 0),
 ]
 
 
