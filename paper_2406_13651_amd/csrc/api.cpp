@@ -577,6 +577,9 @@ clamp_status clamp_fwd_init(const clamp_plan* plan, int32_t scene, const clamp_p
     float2* ypup = static_cast<float2*>(state->y_pupil);
 
     hipError_t e = hipSuccess;
+    // partials of ||D(a) y||^2, added beside the average over the looks
+    const double* sum_part = pci;
+    int sum_count = clampk::col_blocks(s.tab);
     if (s.K > 0) {
         // 3D operator: D(a) y on the cylinder (kept as y_pupil when given),
         // then A^H y = F2^H F_z^H (zero-filled box)
@@ -584,8 +587,8 @@ clamp_status clamp_fwd_init(const clamp_plan* plan, int32_t scene, const clamp_p
         double* pg = at<double>(workspace, s.ws.pzi);
         e = clampk::launch_range_gather(s.tab, L, static_cast<const float2*>(y_full), box,
                                         static_cast<float2*>(state->resid), 1.f - params->mu_init_scale, pg, stream);
-        if (e == hipSuccess && state->ahy2 != nullptr)
-            e = clampk::launch_sum(pg, clampk::gather_blocks(s.tab), L, 1.0, state->ahy2, stream);
+        sum_part = pg;
+        sum_count = clampk::gather_blocks(s.tab);
         clampk::ZArgs za{s.tab, L, box, at<float2>(workspace, s.ws.dfd), at<double>(workspace, s.ws.pzf)};
         if (e == hipSuccess) e = clampk::launch_zpass(+1, za, stream);
         ColArgs ca = col_args(s, L);
@@ -609,11 +612,10 @@ clamp_status clamp_fwd_init(const clamp_plan* plan, int32_t scene, const clamp_p
         ra.img_out = mu;
         e = clampk::launch_row(clampk::ROW_INV, ra, stream);
     }
-    if (e == hipSuccess && s.K == 0 && state->ahy2 != nullptr)
-        e = clampk::launch_sum(pci, clampk::col_blocks(s.tab), L, 1.0, state->ahy2, stream);
-    if (e == hipSuccess) e = clampk::launch_init_r0(n, L, mu, params->mu_init_scale, state->r, pm, stream);
-    if (e == hipSuccess) e = clampk::launch_sum(pm, clampk::mace_blocks(n), 1, 1.0 / (double)n, scal, stream);
-    if (e == hipSuccess) e = clampk::launch_init_floor(n, params->n_agents, scal, state->r, w, stream);
+    if (e == hipSuccess)
+        e = clampk::launch_init_r0(n, L, mu, params->mu_init_scale, state->r, pm, state->ahy2 != nullptr ? L : 0, sum_part,
+                                   sum_count, state->ahy2, stream);
+    if (e == hipSuccess) e = clampk::launch_init_floor(n, params->n_agents, pm, scal, state->r, w, stream);
     return hip_check(e, "clamp_fwd_init launch");
 }
 

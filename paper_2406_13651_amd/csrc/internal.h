@@ -215,13 +215,14 @@ hipError_t launch_diag_after(int nupd, int nres, int looks, const double* part_u
                              const double* part_mace, int nmace, double* conv_err, hipStream_t st);
 // out[i] = a[i] - b[i] over count complex values
 hipError_t launch_csub(size_t count, const float2* a, const float2* b, float2* out, hipStream_t st);
-hipError_t launch_init_r0(size_t n, int looks, float2* mu, float s_mu, float* r0,
-                          double* part, hipStream_t st);
+// and, with sums > 0, sum_out[l] = sum_i sum_part[l * sum_count + i] for l < sums
+hipError_t launch_init_r0(size_t n, int looks, float2* mu, float s_mu, float* r0, double* part, int sums,
+                          const double* sum_part, int sum_count, double* sum_out, hipStream_t st);
 // out[l] = scale * sum_i part[l * count + i] for l < looks
 hipError_t launch_sum(const double* part, int count, int looks, double scale, double* out,
                       hipStream_t st);
-hipError_t launch_init_floor(size_t n, int n_agents, const double* mean_r0, float* r,
-                             float* w, hipStream_t st);
+hipError_t launch_init_floor(size_t n, int n_agents, const double* part, double* mean_r0, float* r, float* w,
+                             hipStream_t st);
 
 struct MaceArgs {
     size_t n;
