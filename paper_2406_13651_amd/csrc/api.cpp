@@ -198,6 +198,7 @@ clamp_status upload_scene(Scene& s) {
     t.nx = s.sc.nx;
     t.ny = s.sc.ny;
     t.nz = s.sc.nz;
+    t.ny_mul = (uint32_t)((1ull << 32) / (uint32_t)s.sc.ny + 1);
     t.P = s.P;
     t.B = s.B;
     t.Bs = s.Bs;

@@ -36,6 +36,7 @@ enum DiagSlot { DG_GAMMA = 0, DG_DD, DG_AD, DG_H0, DG_H1, DG_MURES, DG_WD, DG_R2
 // Device tables of one scene (owned by the plan).
 struct SceneTables {
     int nx, ny, nz;
+    uint32_t ny_mul;  // floor(2^32 / ny) + 1 (slice_of_row)
     int P;       // pupil samples per slice
     int B;       // band columns (columns holding pupil samples)
     int Bs;      // band-buffer values per slice row: tiles * col_tile_cols(ny)

@@ -38,22 +38,87 @@ __host__ __device__ constexpr int row_lds_floats2() {
     return rows_per_block(N) * lds_len<N, kRowPad>();
 }
 
+// The other lane's double in a step of a reduction within rows of 16 lanes
+// (DPP row rotation).
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double x) {
+    const long long b = __builtin_bit_cast(long long, x);
+    const int lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xf, 0xf, false);
+    return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
+}
+// a + b after the upper half of a and the lower half of b (HALF = 32: of the
+// wave; 16: of each half wave) have changed places: the lower half holds the
+// sums of a's halves, the upper half those of b's.
+template <int HALF>
+__device__ __forceinline__ double swap_add_f64(double a, double b) {
+    const unsigned long long ua = __builtin_bit_cast(unsigned long long, a);
+    const unsigned long long ub = __builtin_bit_cast(unsigned long long, b);
+    unsigned alo, ahi, blo, bhi;
+    if constexpr (HALF == 32) {
+        const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)ua, (unsigned)ub, false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
+        alo = lo[0], blo = lo[1], ahi = hi[0], bhi = hi[1];
+    } else {
+        const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)ua, (unsigned)ub, false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
+        alo = lo[0], blo = lo[1], ahi = hi[0], bhi = hi[1];
+    }
+    return __builtin_bit_cast(double, ((unsigned long long)ahi << 32) | alo) +
+           __builtin_bit_cast(double, ((unsigned long long)bhi << 32) | blo);
+}
+// Sums of up to four doubles over the wave: lane 16 i (and its row of 16
+// lanes) returns the sum of value order(i) = {0, 2, 1, 3}.  The first two
+// steps exchange registers and halve the number of values as they halve the
+// lanes that hold them; the row steps are DPP moves.  No LDS instructions:
+// three sums by shuffles were 36 of them and 18 additions, a tenth of the
+// instructions of the gradient pass, which the vector unit bounds (74% busy;
+// 256x256x64, 16 looks: 270 -> 244 us with these sums and slice_of_row).
+template <int K>
+__device__ __forceinline__ double wave_sums_f64(const double (&v)[K]) {
+    static_assert(K >= 1 && K <= 4, "up to four values");
+    const double a = swap_add_f64<32>(v[0], K > 1 ? v[K > 1 ? 1 : 0] : v[0]);
+    double x;
+    if constexpr (K > 2) x = swap_add_f64<16>(a, swap_add_f64<32>(v[2], K > 3 ? v[K > 3 ? 3 : 2] : v[2]));
+    else x = swap_add_f64<16>(a, a);
+    x += dpp_f64<0x128>(x);  // row_ror 8, 4, 2, 1
+    x += dpp_f64<0x124>(x);
+    x += dpp_f64<0x122>(x);
+    x += dpp_f64<0x121>(x);
+    return x;
+}
+// The value whose sum lane row i of wave_sums_f64 holds.
+__host__ __device__ constexpr int wave_sums_slot(int i) { return i == 1 ? 2 : i == 2 ? 1 : i; }
+
+// Each wave's sums of K doubles into red[.][wave] (W waves).
+template <int K, int W>
+__device__ __forceinline__ void wave_sums_store(const double (&v)[K], double (&red)[K][W]) {
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+#pragma unroll
+    for (int k0 = 0; k0 < K; k0 += 4) {
+        double s;
+        if (k0 + 4 <= K) {
+            double q[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) q[k] = v[k0 + k < K ? k0 + k : 0];
+            s = wave_sums_f64<4>(q);
+        } else {
+            constexpr int KR = K % 4 > 0 ? K % 4 : 1;
+            double q[KR];
+#pragma unroll
+            for (int k = 0; k < KR; ++k) q[k] = v[k0 + k < K ? k0 + k : 0];
+            s = wave_sums_f64<KR>(q);
+        }
+        const int slot = k0 + wave_sums_slot(lane >> 4);
+        if ((lane & 15) == 0 && slot < K) red[slot][wid] = s;
+    }
+}
+
 // Sum of K doubles over the block, written by thread 0 to out[0..K).
 template <int K>
-__device__ __forceinline__ void block_sum_store(double (&v)[K], double* out) {
+__device__ __forceinline__ void block_sum_store(const double (&v)[K], double* out) {
     __shared__ double red[K][kBlock / 64];
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        double x = v[k];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
-        v[k] = x;
-    }
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    if (lane == 0) {
-#pragma unroll
-        for (int k = 0; k < K; ++k) red[k][wid] = v[k];
-    }
+    wave_sums_store(v, red);
     __syncthreads();
     if (threadIdx.x == 0) {
 #pragma unroll
@@ -232,6 +297,15 @@ __device__ __forceinline__ float r_update_voxel(const A& a, const BetaVals& bv, 
     return rn;
 }
 
+// row / ny by the plan's reciprocal ny_mul = floor(2^32 / ny) + 1: with e = ny
+// ny_mul - 2^32 <= ny the product's high word exceeds the quotient by at most
+// row e / 2^32 / ny < 1 for any row below 2^31, so by one at most.
+template <class T>
+__device__ __forceinline__ int slice_of_row(const T& s, int row) {
+    const int q = (int)__umulhi((unsigned)row, s.ny_mul);
+    return q * s.ny > row ? q - 1 : q;
+}
+
 // LDS buffers of a row item: twiddles, band position and band column tables
 // (length NX each) and the padded row buffers.
 struct RowLds {
@@ -353,7 +427,8 @@ __device__ __forceinline__ void row_item(const A& a, int look, int rgroup, size_
     const bool active = row < rows;
     const size_t img = ((size_t)look * rows + (active ? row : 0)) * NX;
     const int arow = active ? row : 0;
-    const size_t band = ((size_t)look * s.nz + arow / s.ny) * s.ny * s.Bs + band_row_off(arow % s.ny, s.ny);
+    const int slice = slice_of_row(s, arow);
+    const size_t band = ((size_t)look * s.nz + slice) * s.ny * s.Bs + band_row_off(arow - slice * s.ny, s.ny);
 
     float2 m[FUSED ? PX : 1];
     float rp[FUSED ? PX : 1];
@@ -517,6 +592,7 @@ __device__ __forceinline__ void row_update_mann(const A& a, const F& f, int spli
     const bool active = row < rows;
     const size_t n = (size_t)rows * NX;
     const int arow = active ? row : 0;
+    const int slice = slice_of_row(s, arow);
     const size_t pix = (size_t)arow * NX;
     const int kst = 64 * gpb, kl = gi * 64 + lane;  // keep's stride and this lane's slot
     for (int i = tid; i < NX; i += kBlock) {
@@ -563,7 +639,7 @@ __device__ __forceinline__ void row_update_mann(const A& a, const F& f, int spli
         const int l = l0 + part;
         if (l < a.looks) {
             const size_t img = (size_t)l * n + pix;
-            const size_t band = ((size_t)l * s.nz + arow / s.ny) * s.ny * s.Bs + band_row_off(arow % s.ny, s.ny);
+            const size_t band = ((size_t)l * s.nz + slice) * s.ny * s.Bs + band_row_off(arow - slice * s.ny, s.ny);
             using In = RowIn<NX>;
             float2 in[In::kCount], h[PX];
             {
@@ -623,9 +699,7 @@ __device__ __forceinline__ void row_update_mann(const A& a, const F& f, int spli
             }
             // the wave's share of the look's sum omega |mu'|^2 (no wait for the
             // other waves here)
-            double acc = wm1;
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+            const double acc = wave_sums_f64<1>({(double)wm1});
             if (lane == 0) wsum[l][wave] = acc;
             if (kLockstep && split == 1) __syncthreads();
         }
@@ -952,16 +1026,7 @@ __host__ __device__ inline size_t slice_lds_bytes(int B) {
 template <int K, int NT>
 __device__ __forceinline__ void block_sums(double (&v)[K]) {
     __shared__ double red[K][NT / 64];
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_xor(v[k], off);
-    }
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    if (lane == 0) {
-#pragma unroll
-        for (int k = 0; k < K; ++k) red[k][wid] = v[k];
-    }
+    wave_sums_store(v, red);
     __syncthreads();
     if (threadIdx.x == 0) {
 #pragma unroll
