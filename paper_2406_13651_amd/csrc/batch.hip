@@ -197,8 +197,8 @@ __global__ void kb_set_iter(int* iter, int value, int add) {
 // scenes whose nx is a multiple of TX (gauss3d_tile).
 template <int TX>
 __global__ __launch_bounds__(kBlock) void kb_gauss3d(BatchLaunch b) {
-    __shared__ float tin[gauss_in_floats<TX>()];
-    __shared__ float txf[gauss_xf_floats<TX>()];
+    __shared__ __align__(16) float tin[2][gauss_in_floats<TX>()];
+    __shared__ __align__(16) float txf[2][gauss_xf_floats<TX>()];
     const BatchItem w = const_ref(b.queue[TX == 64 ? Q_PRIOR64 : Q_PRIOR32] + blockIdx.x);
     gauss3d_tile<TX>(const_ref(&b.scenes[w.scene].prior), w.b, tin, txf);
 }

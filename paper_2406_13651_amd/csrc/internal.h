@@ -300,7 +300,7 @@ struct DiagArgs {
 
 // The Gaussian prior agent of one volume (gauss3d_tile): output tiles of
 // kGaussTY rows by 64 or 32 x-voxels over kGaussCZ range slices.
-constexpr int kGaussTY = 8, kGaussCZ = 8;
+constexpr int kGaussTY = 8, kGaussCZ = 4;
 template <int TX>
 __host__ __device__ inline int gauss_tiles(int nx, int ny, int nz) {
     return (nx / TX) * (ny / kGaussTY) * ((nz + kGaussCZ - 1) / kGaussCZ);

@@ -400,8 +400,8 @@ __global__ __launch_bounds__(kBlock) void k_mace_final(const double* part, int b
 // neighbouring tiles share an L2, measured 1-2 us slower at 256x256x64.)
 template <int TX>
 __global__ __launch_bounds__(kBlock) void k_gauss3d(PriorArgs p) {
-    __shared__ float tin[gauss_in_floats<TX>()];
-    __shared__ float txf[gauss_xf_floats<TX>()];
+    __shared__ __align__(16) float tin[2][gauss_in_floats<TX>()];
+    __shared__ __align__(16) float txf[2][gauss_xf_floats<TX>()];
     gauss3d_tile<TX>(p, blockIdx.x, tin, txf);
 }
 

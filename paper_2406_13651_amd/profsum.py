@@ -47,7 +47,7 @@ KERNEL_SOURCES = {
 # kernel name pattern -> timing stage (first match wins)
 STAGE_OF = [
     (r"k_row_upd_mann", "row_update_mann"),
-    (r"k_row_grad<", "row_grad"),
+    (r"k_row_grad<|k_slice_grad<", "row_grad"),
     (r"k_row<\d+, 3>|k_row<\d+, 4>", "row_update"),
     (r"k_col_inv_compact<", "col_inv"),
     (r"k_col_fwd<", "col_fwd"),
