@@ -273,7 +273,8 @@ __device__ __forceinline__ void fft_regs_stages(float2 (&h)[N / T], float2* buf,
 // Unnormalised length-N DFT (see fft_regs_ok) of the group's vector, held in
 // h (IN_REGS) or in buf[pos(i)]; the result goes to h (OUT_REGS) or to buf in
 // natural order, visible to the group.  Starts with a group synchronisation,
-// so earlier reads and writes of buf by the group are done.
+// so earlier reads and writes of buf by the group are done, and synchronises
+// after its last reads, so the caller may write buf at once.
 template <int N, int T, int S, bool IN_REGS, bool OUT_REGS, bool WAVE, class Pos>
 __device__ __forceinline__ void fft_regs_at(float2 (&h)[N / T], float2* buf, Pos pos, int t, const float2* tw) {
     static_assert(fft_len_ok(N) && fft_regs_ok<N, T>(), "length and group size outside the register form");
@@ -368,7 +369,8 @@ __device__ __forceinline__ void fft_head_stages(float2* buf, int t, const float2
 // r N / R0 of the vector on the threads t < N / R0 (the others' are not
 // used).  The result goes to h (h[k] = element t + k T) and, unless OUT_REGS,
 // from there to buf in natural order, visible to the group.  Starts with a
-// group synchronisation, so earlier reads and writes of buf are done.
+// group synchronisation, so earlier reads and writes of buf are done, and
+// synchronises after its last reads, so the caller may write buf at once.
 template <int N, int T, int S, int PADSH, bool OUT_REGS, bool WAVE>
 __device__ __forceinline__ void fft_split(float2 (&v)[radix_at(N, 0)], float2 (&h)[N / T], float2* buf, int t,
                                           const float2* tw) {
@@ -385,9 +387,9 @@ __device__ __forceinline__ void fft_split(float2 (&v)[radix_at(N, 0)], float2 (&
     fft_head_stages<N, T, S, PADSH, 1, TAIL, WAVE>(buf, t, tw);
 #pragma unroll
     for (int k = 0; k < N / T; ++k) h[k] = buf[lds_pos<PADSH>(t + k * T)];
+    group_sync<WAVE>();
     fft_tail_stages<N, T, S, TAIL>(h, t, tw);
     if constexpr (!OUT_REGS) {
-        group_sync<WAVE>();
 #pragma unroll
         for (int k = 0; k < N / T; ++k) buf[lds_pos<PADSH>(t + k * T)] = h[k];
         group_sync<WAVE>();

@@ -693,7 +693,9 @@ __device__ __forceinline__ void row_update_mann(const A& a, const F& f, int spli
                             const float e = rn - wb[k * kst + kl];
                             e2[k] = fmaf(e, e, e2[k]);
                         } else {
-                            rx[k * 64 + lane] = rn;  // the transform's readers of the row are this wave
+                            // over elements that other lanes of the wave took the transform's
+                            // last inputs from: the transform synchronised after reading them
+                            rx[k * 64 + lane] = rn;
                         }
                         wm1 += om * cabs2(m1);
                     }
