@@ -422,8 +422,12 @@ __device__ __forceinline__ void row_item(const A& a, int look, int rgroup, size_
     // runs near the read/write bandwidth ceiling and loads its streams late.
     constexpr bool PREFETCH = (MODE == ROW_GRAD);
     const auto& s = a.s;
-    const int tid = threadIdx.x;
-    const int ri = tid / TR, t = tid % TR;
+    const int tid = threadIdx.x, t = tid % TR;
+    // a row that fills its wave (384 and 512 points) has wave-uniform indices
+    // and base addresses, held in scalar registers: 76 vector registers in the
+    // 512-point gradient pass, where 80 were not enough at six waves and one
+    // went to scratch (512x512x64, 8 looks: 486 -> 456 us)
+    const int ri = TR == 64 ? __builtin_amdgcn_readfirstlane(tid / TR) : tid / TR;
     const int rows = s.nz * s.ny;
     const int row = rgroup * RPB + ri;
     const bool active = row < rows;
