@@ -1187,6 +1187,12 @@ clamp_status clamp_batch_create(const clamp_plan* plan, const clamp_batch_scene*
     // still fits on the chip at once, else each wave walks every look
     long blocks4[kSizeClasses] = {};
     for (const Scene& s : plan->scenes) blocks4[length_class(s.sc.nx)] += mann_blocks(s.tab, 4);
+    // voxels that the Gaussian prior's launches of 64- and 32-voxel tiles smooth
+    size_t prior_voxels[2] = {0, 0};
+    for (int i = 0; i < ns; ++i)
+        if (scenes[i].params.n_agents == plan->scenes[i].sc.looks + 1)
+            prior_voxels[plan->scenes[i].sc.nx % 64 == 0 ? 0 : 1] += plan->scenes[i].n();
+    const int gauss_cz[2] = {gauss_slices(prior_voxels[0]), gauss_slices(prior_voxels[1])};
     size_t ws_off = 0;
     for (int i = 0; i < ns; ++i) {
         const Scene& s = plan->scenes[i];
@@ -1305,8 +1311,7 @@ clamp_status clamp_batch_create(const clamp_plan* plan, const clamp_batch_scene*
         if (with_prior) {
             // output tiles of the single-pass Gaussian (gauss3d_tile)
             const int tx = s.sc.nx % 64 == 0 ? 64 : 32;
-            const int tiles = tx == 64 ? gauss_tiles<64>(s.sc.nx, s.sc.ny, s.sc.nz)
-                                       : gauss_tiles<32>(s.sc.nx, s.sc.ny, s.sc.nz);
+            const int tiles = gauss_tiles(tx, gauss_cz[tx == 64 ? 0 : 1], s.sc.nx, s.sc.ny, s.sc.nz);
             for (int c = 0; c < tiles; ++c) q[tx == 64 ? Q_PRIOR64 : Q_PRIOR32].push_back(BatchItem{i, 0, c, 0});
         }
     }
@@ -1316,6 +1321,7 @@ clamp_status clamp_batch_create(const clamp_plan* plan, const clamp_batch_scene*
     b->cus = device_cus();
     b->fused = fused;
     BatchLaunch& L = b->launch;
+    for (int k = 0; k < 2; ++k) L.gauss_cz[k] = gauss_cz[k];
     for (int side = 0; side < 3; ++side) {
         std::vector<BatchItem>* by = side == 0 ? rows_by_len : side == 1 ? cols_by_len : rowg_by_len;
         std::vector<BatchItem>& dst = q[side == 0 ? Q_ROW : side == 1 ? Q_COL : Q_ROWG];

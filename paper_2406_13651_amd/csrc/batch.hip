@@ -195,12 +195,12 @@ __global__ void kb_set_iter(int* iter, int value, int add) {
 
 // Gaussian prior agents: one block per output tile (scene, tile) of the
 // scenes whose nx is a multiple of TX (gauss3d_tile).
-template <int TX>
+template <int TX, int CZ>
 __global__ __launch_bounds__(kBlock) void kb_gauss3d(BatchLaunch b) {
     __shared__ __align__(16) float tin[2][gauss_in_floats<TX>()];
     __shared__ __align__(16) float txf[2][gauss_xf_floats<TX>()];
     const BatchItem w = const_ref(b.queue[TX == 64 ? Q_PRIOR64 : Q_PRIOR32] + blockIdx.x);
-    gauss3d_tile<TX>(const_ref(&b.scenes[w.scene].prior), w.b, tin, txf);
+    gauss3d_tile<TX, CZ>(const_ref(&b.scenes[w.scene].prior), w.b, tin, txf);
 }
 
 hipError_t batch_set_iter(int* iter, int value, hipStream_t st) {
@@ -280,8 +280,10 @@ hipError_t batch_stage(int stage, const BatchLaunch& b, hipStream_t st) {
         case BS_RESID: go(Q_RESID, kb_resid); break;
         case BS_DIAG: go(Q_LOOK, kb_diag); break;
         case BS_PRIOR:
-            go(Q_PRIOR64, kb_gauss3d<64>);
-            go(Q_PRIOR32, kb_gauss3d<32>);
+            if (b.gauss_cz[0] == 8) go(Q_PRIOR64, kb_gauss3d<64, 8>);
+            else go(Q_PRIOR64, kb_gauss3d<64, 4>);
+            if (b.gauss_cz[1] == 8) go(Q_PRIOR32, kb_gauss3d<32, 8>);
+            else go(Q_PRIOR32, kb_gauss3d<32, 4>);
             break;
         case BS_ROW_UPDATE_MANN: launch_rowg_segments(b, st); break;
         case BS_MACE: go(Q_VOX, kb_mace); break;

@@ -299,11 +299,17 @@ struct DiagArgs {
 };
 
 // The Gaussian prior agent of one volume (gauss3d_tile): output tiles of
-// kGaussTY rows by 64 or 32 x-voxels over kGaussCZ range slices.
-constexpr int kGaussTY = 8, kGaussCZ = 4;
-template <int TX>
-__host__ __device__ inline int gauss_tiles(int nx, int ny, int nz) {
-    return (nx / TX) * (ny / kGaussTY) * ((nz + kGaussCZ - 1) / kGaussCZ);
+// kGaussTY rows by 64 or 32 x-voxels over 4 or 8 range slices.  A tile of 8
+// reads 1.8 times its output where one of 4 reads 2.5 times, but takes longer
+// from its first load to its last store: 8 once the launch (one volume, or a
+// batch's volumes of one tile width) holds 2^22 voxels, 16 blocks' worth per
+// CU.  With 4 and with 8: 128^3 13.9 and 14.4 us, 256x256x32 14.0 and 14.7;
+// 256x256x64 22.5 and 21.3, 192x192x128 24.6 and 23.8, 512x512x64 73 and 65,
+// 512x512x128 141 and 119.
+constexpr int kGaussTY = 8;
+constexpr int gauss_slices(size_t voxels) { return voxels >= ((size_t)1 << 22) ? 8 : 4; }
+__host__ __device__ inline int gauss_tiles(int tx, int cz, int nx, int ny, int nz) {
+    return (nx / tx) * (ny / kGaussTY) * ((nz + cz - 1) / cz);
 }
 struct PriorArgs {
     int nx, ny, nz;
@@ -348,6 +354,7 @@ struct BatchLaunch {
     int seg_grid[3][kSizeClasses];
     int nseg[3];
     int mann_split[kSizeClasses];  // waves per row group in a segment of the fused update pass (1 or 4)
+    int gauss_cz[2];            // range slices of a tile in Q_PRIOR64 and Q_PRIOR32 (gauss_slices)
     const float* beta_table;    // device [beta_len]
     int beta_len;
     int* iter;                  // device iteration counter (iterations done)

@@ -394,15 +394,15 @@ __global__ __launch_bounds__(kBlock) void k_mace_final(const double* part, int b
 // ---------------------------------------------------------------------------
 // The periodic separable 7-tap smoothing of a volume in one pass, one block
 // per output tile (gauss3d_tile).  Each input element is fetched about
-// (GTY + 6)(TX + 6)/(GTY TX) (GCZ + 6)/GCZ times and the output written
+// (GTY + 6)(TX + 6)/(GTY TX) (CZ + 6)/CZ times and the output written
 // once, where three separate passes read and write the volume three times.
 // (Dealing the tiles to the eight XCDs in contiguous runs, so that
 // neighbouring tiles share an L2, measured 1-2 us slower at 256x256x64.)
-template <int TX>
+template <int TX, int CZ>
 __global__ __launch_bounds__(kBlock) void k_gauss3d(PriorArgs p) {
     __shared__ __align__(16) float tin[2][gauss_in_floats<TX>()];
     __shared__ __align__(16) float txf[2][gauss_xf_floats<TX>()];
-    gauss3d_tile<TX>(p, blockIdx.x, tin, txf);
+    gauss3d_tile<TX, CZ>(p, blockIdx.x, tin, txf);
 }
 
 // ---------------------------------------------------------------------------
@@ -699,10 +699,12 @@ hipError_t launch_gauss(int nx, int ny, int nz, const float* taps7, const float*
     p.in = in;
     p.out = out;
     if (ny % kGaussTY != 0 || nx % 32 != 0) return hipErrorInvalidValue;
-    if (nx % 64 == 0)
-        hipLaunchKernelGGL(k_gauss3d<64>, dim3(gauss_tiles<64>(nx, ny, nz)), dim3(kBlock), 0, st, p);
-    else
-        hipLaunchKernelGGL(k_gauss3d<32>, dim3(gauss_tiles<32>(nx, ny, nz)), dim3(kBlock), 0, st, p);
+    const int tx = nx % 64 == 0 ? 64 : 32, cz = gauss_slices((size_t)nx * ny * nz);
+    const dim3 grid(gauss_tiles(tx, cz, nx, ny, nz));
+    if (tx == 64 && cz == 8) hipLaunchKernelGGL((k_gauss3d<64, 8>), grid, dim3(kBlock), 0, st, p);
+    else if (tx == 64) hipLaunchKernelGGL((k_gauss3d<64, 4>), grid, dim3(kBlock), 0, st, p);
+    else if (cz == 8) hipLaunchKernelGGL((k_gauss3d<32, 8>), grid, dim3(kBlock), 0, st, p);
+    else hipLaunchKernelGGL((k_gauss3d<32, 4>), grid, dim3(kBlock), 0, st, p);
     return hipGetLastError();
 }
 

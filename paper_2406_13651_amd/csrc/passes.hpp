@@ -1373,11 +1373,11 @@ __device__ __forceinline__ void mace_voxel(const MaceArgs& a, const float* ups, 
 
 // Periodic 7-tap Gaussian smoothing along z, y and x in one pass over the
 // volume: one call produces an output tile of kGaussTY rows x TX voxels over
-// range slices z0 .. z0 + kGaussCZ - 1.  Tiles are numbered z chunk fastest,
+// CZ range slices z0 .. z0 + CZ - 1.  Tiles are numbered z chunk fastest,
 // then x, then y: tile t has bz = t % zc, bx = (t / zc) % (nx / TX),
 // by = t / (zc nx / TX), so that consecutive tiles share their halos.  Every
 // (kGaussTY + 6) x (TX + 6) window of the input slices z0 - 3 .. z0 +
-// kGaussCZ + 2 is loaded into registers up front, so that the block waits
+// CZ + 2 is loaded into registers up front, so that the block waits
 // for memory once, not once per slice, and is filtered along z there, each
 // thread over its own window positions.  The z-filtered window goes to LDS and
 // is filtered along x, then along y (the separable filter's three passes
@@ -1385,10 +1385,9 @@ __device__ __forceinline__ void mace_voxel(const MaceArgs& a, const float* ups, 
 // z, slice o - 1 along x and slice o - 2 along y, with one barrier per phase
 // and both LDS windows double-buffered.  A thread filters four adjacent x (ten
 // LDS values in three 16-byte reads) and adjacent rows of one column, instead of
-// seven values read per result: a tile's serial chain, not its traffic, is
-// what bounds the pass (128^3: 17.7 -> 15.1 us, 384x192x37: 20.0 -> 18.3,
-// 256x256x64: 20.5 -> 19.0; the same phases over eight slices a tile: 16.5,
-// 19.1 and 19.2).
+// seven values read per result: a tile's serial chain bounds the pass on small
+// volumes (128^3: 17.7 -> 15.1 us, 384x192x37: 20.0 -> 18.3), the windows'
+// traffic on large ones (gauss_slices).
 // p holds nx, ny, nz (ny a multiple of kGaussTY, nx of TX), the taps g[7], in
 // and out (not overlapping).
 template <int TX>
@@ -1405,13 +1404,13 @@ __device__ __forceinline__ void for_each_index(F& f) {
     }
 }
 
-template <int TX, class P>
+template <int TX, int CZ, class P>
 __device__ __forceinline__ void gauss3d_tile(const P& p, int tile, float (&tin)[2][gauss_in_floats<TX>()],
                                              float (&txf)[2][gauss_xf_floats<TX>()]) {
     constexpr int W = TX + 6, WS = TX + 8, H = kGaussTY + 6;  // window, its row stride in LDS
     constexpr int NIN = H * W;
     constexpr int LPT = (NIN + kBlock - 1) / kBlock;
-    constexpr int NZW = kGaussCZ + 6;  // input slices of a chunk
+    constexpr int NZW = CZ + 6;  // input slices of a chunk
     constexpr int XT = H * TX / 4;                                          // threads of the x filter
     constexpr int OPT = kGaussTY * TX / kBlock > 1 ? kGaussTY * TX / kBlock : 1;  // rows per thread of the y filter
     static_assert(XT <= kBlock && kGaussTY % OPT == 0 && kGaussTY / OPT * TX <= kBlock, "a tile divides among the threads");
@@ -1422,10 +1421,10 @@ __device__ __forceinline__ void gauss3d_tile(const P& p, int tile, float (&tin)[
 #pragma unroll
     for (int k = 0; k < 7; ++k) g[k] = p.g[k];
     const int tid = threadIdx.x;
-    const int zc = (nz + kGaussCZ - 1) / kGaussCZ, tx = nx / TX;
+    const int zc = (nz + CZ - 1) / CZ, tx = nx / TX;
     const int bz = tile % zc, bx = (tile / zc) % tx, by = tile / (zc * tx);
-    const int x0 = bx * TX, y0 = by * kGaussTY, z0 = bz * kGaussCZ;
-    const int slices = z0 + kGaussCZ < nz ? kGaussCZ : nz - z0;
+    const int x0 = bx * TX, y0 = by * kGaussTY, z0 = bz * CZ;
+    const int slices = z0 + CZ < nz ? CZ : nz - z0;
     const unsigned slice = (unsigned)nx * (unsigned)ny;
     unsigned goff[LPT];
     int loff[LPT];
@@ -1457,7 +1456,7 @@ __device__ __forceinline__ void gauss3d_tile(const P& p, int tile, float (&tin)[
     auto phase = [&](auto phase_index) {
         constexpr int o = decltype(phase_index)::value;
         if (o >= slices + 2) return;  // uniform over the block
-        if constexpr (o < kGaussCZ) {
+        if constexpr (o < CZ) {
             if (o < slices) {
 #pragma unroll
                 for (int j = 0; j < LPT; ++j) {
@@ -1498,7 +1497,7 @@ __device__ __forceinline__ void gauss3d_tile(const P& p, int tile, float (&tin)[
         }
         __syncthreads();
     };
-    for_each_index<kGaussCZ + 2>(phase);
+    for_each_index<CZ + 2>(phase);
 }
 
 }  // namespace clampk
