@@ -271,7 +271,7 @@ def run_batch(args):
     for name, (ms, cnt) in stages.items():
         avg = ms / cnt
         e = {"avg_ms": round(avg, 4), "launches": cnt}
-        if name in sb:
+        if name in sb and avg > 0:
             e["alg_GBps"] = round(sb[name] / (avg * 1e-3) / 1e9, 1)
         per_stage[name] = e
     dom = max((k for k in per_stage if k in sb), key=lambda k: stages[k][0])
@@ -591,7 +591,7 @@ def large_eval(args, dev, prior=None):
     per_stage = {}
     for name, (ms, cnt) in stages.items():
         e = {"avg_ms": round(ms / cnt, 4), "launches": cnt}
-        if name in sb:
+        if name in sb and ms > 0:
             e["alg_GBps"] = round(sb[name] / (ms / cnt * 1e-3) / 1e9, 1)
         per_stage[name] = e
     dom_ms = stages[dom][0] / stages[dom][1]
@@ -996,7 +996,7 @@ def run_padded(args):
         per = {}
         for k, (ms, cnt) in stages.items():
             e = {"avg_ms": round(ms / cnt, 4)}
-            if k in sb:
+            if k in sb and ms > 0:
                 e["alg_GBps"] = round(sb[k] / (ms / cnt * 1e-3) / 1e9, 1)
             per[k] = e
         rows[name] = {"nz": nz, "range_support": g.scene.range_support, "alpha": info["alpha"],
@@ -1139,7 +1139,7 @@ def main():
     for name, (ms, cnt) in stages.items():
         avg = ms / cnt
         entry = {"avg_ms": round(avg, 5), "launches": cnt}
-        if name in sb:
+        if name in sb and avg > 0:
             entry["alg_bytes"] = sb[name]
             entry["alg_GBps"] = round(sb[name] / (avg * 1e-3) / 1e9, 1)
         per_stage[name] = entry
@@ -1154,7 +1154,9 @@ def main():
                          "resid_update", "diag_after")
     # the per-stage events of the breakdown add a few percent to each stage,
     # so the agents' time is the clean timed iteration less the stages that
-    # are not the forward agents' (prior and the Mann step's own launch)
+    # are not the forward agents' (the prior, and the Mann step where it has a
+    # launch of its own; fused, its final sums run in the diagnostics launch
+    # and the stage is counted without time)
     other_ms = sum(stages[k][0] / stages[k][1] for k in stages if k not in agent_stage_names)
     mann_ms = stages["mace_step"][0] / stages["mace_step"][1] if "mace_step" in stages else 0.0
     agent_ms = elapsed / args.steps * 1e3 - other_ms
@@ -1189,12 +1191,13 @@ def main():
         "iters_per_s": args.steps / elapsed,
         # the lower bound (48 + 32 alpha bytes per voxel-look) counts the Mann
         # update's w traffic as fused into the agent's last pass, as the fused
-        # update pass does (the Mann step's own launch is then only its final
-        # reduction, counted in the second figure)
+        # update pass does (its final sums run in the diagnostics launch; the
+        # second figure adds a Mann step launched on its own, where there is one)
         "fwd_agent": agent_roof(agent_ms, "forward-agent stages (col_inv .. diag_after, the update pass with the "
                                           "Mann step fused in): the timed iteration less the other stages' "
                                           "breakdown means, against the lower bound of one application"),
-        "fwd_agent_with_mann": agent_roof(agent_ms + mann_ms, "forward-agent stages plus the Mann step's launch"),
+        "fwd_agent_with_mann": agent_roof(agent_ms + mann_ms, "forward-agent stages plus the Mann step's launch "
+                                                         "(none when it is fused)"),
         "stages": per_stage,
         "conv_err": conv,
         "nrmse": nrmse,

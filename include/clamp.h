@@ -510,7 +510,7 @@ clamp_status clamp_unet_adam_step(clamp_unet* unet, float lr, void* hip_stream);
  * writes the summed milliseconds and launch counts of each stage
  * (HOST arrays of CLAMP_STAGES entries, see clamp_stage_name) and forgets
  * the records.  A stage whose work a call does in another stage's launch is
- * counted without time.  Enabling timing makes the plan unsafe to share between
+ * counted without time, and no events are recorded for it.  Enabling timing makes the plan unsafe to share between
  * threads.  Creating events can fail with CLAMP_EDEVICE. */
 #define CLAMP_STAGES 15
 clamp_status clamp_plan_set_timing(clamp_plan* plan, int32_t enable);
