@@ -56,9 +56,9 @@ size_t cnn_wq_elems(int cinp);
 hipError_t cnn_pack(const float* x, const float* scale, long nvox, uint16_t* x8, hipStream_t st);
 int cnn_reduce_blocks(long nvox);
 hipError_t cnn_mean(const float* x, long nvox, double* part, float* mean, hipStream_t st);
-// Squared error, and its gradient in fp32 (g1) and in the 8-channel bf16 form (g8).
-hipError_t cnn_loss(const float* out, const float* target, long nvox, uint16_t* g8, float* g1, double* part,
-                    double* loss, hipStream_t st);
+// Squared error, and its gradient in fp32 (over out) and in the 8-channel bf16 form (g8).
+hipError_t cnn_loss(float* out, const float* target, long nvox, uint16_t* g8, double* part, double* loss,
+                    hipStream_t st);
 int cnn_wgrad_grid();
 size_t cnn_wgrad_part_bytes();
 // Weight gradient gw[27][32][32] and bias gradient gb[32] of one layer.

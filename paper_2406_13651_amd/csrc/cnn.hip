@@ -805,9 +805,10 @@ __global__ __launch_bounds__(kCnnBlock) void k_mean_final(const double* part, in
     if (threadIdx.x == 0) *mean = (float)(tot[0] / (double)nvox);
 }
 
-// Squared error partials and the output gradient 2 (out - t) / nvox.
-__global__ __launch_bounds__(kCnnBlock) void k_loss(const float* out, const float* target, long nvox, uint16_t* g8,
-                                                    float* g1, double* part) {
+// Squared error partials and the output gradient 2 (out - t) / nvox, which
+// takes the output's place.
+__global__ __launch_bounds__(kCnnBlock) void k_loss(float* out, const float* target, long nvox, uint16_t* g8,
+                                                    double* part) {
     const float c = (float)(2.0 / (double)nvox);
     double s = 0.0;
     for (long v = (long)blockIdx.x * kCnnBlock + threadIdx.x; v < nvox; v += (long)gridDim.x * kCnnBlock) {
@@ -816,7 +817,7 @@ __global__ __launch_bounds__(kCnnBlock) void k_loss(const float* out, const floa
         uint4 q = make_uint4(0u, 0u, 0u, 0u);
         q.x = f2bf(c * r);
         reinterpret_cast<uint4*>(g8)[v] = q;
-        g1[v] = c * r;
+        out[v] = c * r;
     }
     double a[1] = {s};
     cnn_block_sum<1>(a, part + blockIdx.x);
@@ -1528,10 +1529,10 @@ hipError_t cnn_mean(const float* x, long nvox, double* part, float* mean, hipStr
     return hipGetLastError();
 }
 
-hipError_t cnn_loss(const float* out, const float* target, long nvox, uint16_t* g8, float* g1, double* part,
-                    double* loss, hipStream_t st) {
+hipError_t cnn_loss(float* out, const float* target, long nvox, uint16_t* g8, double* part, double* loss,
+                    hipStream_t st) {
     const int nb = cnn_reduce_blocks(nvox);
-    hipLaunchKernelGGL(k_loss, dim3(nb), dim3(kCnnBlock), 0, st, out, target, nvox, g8, g1, part);
+    hipLaunchKernelGGL(k_loss, dim3(nb), dim3(kCnnBlock), 0, st, out, target, nvox, g8, part);
     hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(kCnnBlock), 0, st, part, nb, nvox, loss);
     return hipGetLastError();
 }

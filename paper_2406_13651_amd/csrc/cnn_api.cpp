@@ -54,7 +54,7 @@ clamp_status hip_check(hipError_t e, const char* what) {
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Layout {
-    size_t x8, act[kLayers], bits[kLayers], out, g8, g1, ga, gb, mean, part, wpart, total;
+    size_t x8, act[kLayers], bits[kLayers], out, g8, ga, gb, mean, part, wpart, total;
 };
 
 Layout layout(long nvox, bool train) {
@@ -71,7 +71,6 @@ Layout layout(long nvox, bool train) {
         for (int l = 1; l < kLayers; ++l) L.bits[l] = take(nvox * 4);
         L.out = take(nvox * 4);
         L.g8 = take(nvox * 16);
-        L.g1 = take(nvox * 4);
         L.ga = take(nvox * 64);
         L.gb = take(nvox * 64);
         L.wpart = take(clampk::cnn_wgrad_part_bytes());
@@ -301,8 +300,8 @@ clamp_status clamp_cnn_grad(clamp_cnn* cnn, const float* x, const float* target,
     hipError_t e = forward(cnn, x, out, nullptr, nvol, nz, ny, nx, at<uint16_t>(workspace, L.x8), acts, bits, nullptr,
                            nullptr, s);
     uint16_t* g8 = at<uint16_t>(workspace, L.g8);
-    float* g1 = at<float>(workspace, L.g1);
-    if (e == hipSuccess) e = clampk::cnn_loss(out, target, nvox, g8, g1, at<double>(workspace, L.part), loss, s);
+    if (e == hipSuccess) e = clampk::cnn_loss(out, target, nvox, g8, at<double>(workspace, L.part), loss, s);
+    const float* g1 = out;  // dL/dout
     // backward: g holds dL/dz_l with channels coutp_of(l) (8 for the last layer)
     const uint16_t* gl = g8;
     uint16_t* gbuf[2] = {at<uint16_t>(workspace, L.ga), at<uint16_t>(workspace, L.gb)};

@@ -270,7 +270,7 @@ int level_of(int l) { return l < 2 * kLevels ? l / 2 : (4 * kLevels - 1 - l) / 2
 
 // Workspace of a training step: every tensor the backward pass reads.
 struct TrainLayout {
-    size_t x8, out, g8, g1, z[kConvs], a[kConvs], bits[kConvs], p[kLevels + 1], s[kLevels], gs[kLevels], G[kLevels][3], gp3;
+    size_t x8, out, g8, z[kConvs], a[kConvs], bits[kConvs], p[kLevels + 1], s[kLevels], gs[kLevels], G[kLevels][3], gp3;
     size_t bn, coef, chanpart, uppart, wpart, part, total;
 };
 
@@ -287,7 +287,6 @@ TrainLayout train_layout(long nvox) {
     L.x8 = take(nvox * 16);
     L.out = take(nvox * 4);
     L.g8 = take(nvox * 16);
-    L.g1 = take(nvox * 4);
     for (int l = 0; l < kConvs; ++l) {
         L.z[l] = take(nv[level_of(l)] * 64);
         L.a[l] = take(nv[level_of(l)] * 64);
@@ -445,11 +444,10 @@ hipError_t train_step(clamp_unet* u, const float* x, const float* target, int32_
         e = clampk::cnn_conv(kWidth, clampk::EPI_FINAL, a, st);
     }
     uint16_t* g8 = B(L.g8);
-    float* g1 = T.buf<float>(L.g1);
-    if (e == hipSuccess) e = clampk::cnn_loss(out, target, nvox, g8, g1, T.buf<double>(L.part), loss, st);
-    // backward: final layer
+    if (e == hipSuccess) e = clampk::cnn_loss(out, target, nvox, g8, T.buf<double>(L.part), loss, st);
+    // backward: final layer (out now holds dL/dout)
     if (e == hipSuccess)
-        e = clampk::cnn_wgrad_one(0, nvol, nz, ny, nx, g1, B(L.a[kConvs - 1]), T.buf<float>(L.wpart), g + final_w(),
+        e = clampk::cnn_wgrad_one(0, nvol, nz, ny, nx, out, B(L.a[kConvs - 1]), T.buf<float>(L.wpart), g + final_w(),
                                   g + final_b(), st);
     uint16_t* gcur = B(L.G[0][0]);
     if (e == hipSuccess) {

@@ -47,3 +47,13 @@ def test_tv_prior_shares_the_agents_workspace(fused):
         h = oracle.clamp_iteration(st, y, mask, f32(s2w), f32(1e-3), 0.5, lambda v: oracle.tv_prox(v, lam, 3)[0])
     assert report("tv run wbar fused=%d" % fused, rel_l2(g.wbar.cpu().numpy(), h["wbar"]), 1e-5) <= 1e-5
     assert report("tv run mu fused=%d" % fused, rel_l2(g.mu.cpu().numpy(), st.mu), 1e-5) <= 1e-5
+
+
+def test_cnn_training_workspace():
+    """Bytes a voxel of a training step: the packed input, seven activations of
+    32 channels and their ReLU patterns, the output (which its gradient
+    replaces), the output gradient in 8 channels, two gradients of 32."""
+    from paper_2406_13651_amd import _clamp as C
+    v = 32 * 64 * 64
+    per = (C.clamp_cnn_workspace_size(24, 32, 64, 64, True) - C.clamp_cnn_workspace_size(12, 32, 64, 64, True)) / (12 * v)
+    assert per <= 16 + 7 * 64 + 7 * 4 + 4 + 16 + 2 * 64 + 0.01
