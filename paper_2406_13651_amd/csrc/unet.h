@@ -62,7 +62,7 @@ hipError_t unet_chan_finalize(int mode, const double* part, int blocks, long m, 
                               float* mean, float* rstd, float* A, float* B, float* C, float* run_mean,
                               float* run_var, float* out0, float* out1, hipStream_t st);
 // out = bf16([ReLU](A x + B y + C)) per channel (Y may be NULL: no B y term),
-// and with relu its ReLU pattern (cnn.h) into bits.
+// and with relu its ReLU pattern (cnn.h) into bits, unless that is NULL.
 hipError_t unet_affine(const uint16_t* X, const uint16_t* Y, const float* A, const float* B, const float* C, int relu,
                        long nvox, uint16_t* out, uint16_t* bits, hipStream_t st);
 // de = [e > 0] (dp routed to each window's first maximum + dskip) (fine sizes).

@@ -345,9 +345,9 @@ __global__ __launch_bounds__(1024) void k_chan_finalize(int mode, const double* 
 }
 
 // out = bf16([ReLU](A x + B y + C)) per channel over a bf16 [nvox][32] tensor
-// (y only when HAS_Y).  With RELU the pattern of positive outputs goes to
+// (y only when HAS_Y).  With BITS the pattern of positive outputs goes to
 // bits: this thread's channels 8 j .. 8 j + 7 are byte j / 2 of word j % 2.
-template <bool HAS_Y, bool RELU>
+template <bool HAS_Y, bool RELU, bool BITS>
 __global__ __launch_bounds__(kBlock) void k_affine(const uint16_t* X, const uint16_t* Y, const float* A,
                                                    const float* B, const float* Cc, long nvox, uint16_t* out,
                                                    uint8_t* bits) {
@@ -373,7 +373,7 @@ __global__ __launch_bounds__(kBlock) void k_affine(const uint16_t* X, const uint
         }
         const uint4 q = pack8(o);
         *reinterpret_cast<uint4*>(out + i * 8) = q;
-        if constexpr (RELU) {
+        if constexpr (BITS) {
             const uint32_t d[4] = {q.x, q.y, q.z, q.w};
             uint32_t b = 0u;
 #pragma unroll
@@ -695,10 +695,12 @@ hipError_t unet_affine(const uint16_t* X, const uint16_t* Y, const float* A, con
                        long nvox, uint16_t* out, uint16_t* bits, hipStream_t st) {
     const dim3 g(grid_of(nvox * 4, 1 << 20)), b(kBlock);
     uint8_t* bb = reinterpret_cast<uint8_t*>(bits);
-    if (Y != nullptr && relu) hipLaunchKernelGGL((k_affine<true, true>), g, b, 0, st, X, Y, A, B, C, nvox, out, bb);
-    else if (Y != nullptr) hipLaunchKernelGGL((k_affine<true, false>), g, b, 0, st, X, Y, A, B, C, nvox, out, bb);
-    else if (relu) hipLaunchKernelGGL((k_affine<false, true>), g, b, 0, st, X, Y, A, B, C, nvox, out, bb);
-    else hipLaunchKernelGGL((k_affine<false, false>), g, b, 0, st, X, Y, A, B, C, nvox, out, bb);
+#define AFFINE(Y_, R_, B_) hipLaunchKernelGGL((k_affine<Y_, R_, B_>), g, b, 0, st, X, Y, A, B, C, nvox, out, bb)
+    if (Y == nullptr && relu && bb != nullptr) AFFINE(false, true, true);
+    else if (Y == nullptr && relu) AFFINE(false, true, false);
+    else if (Y != nullptr && !relu && bb == nullptr) AFFINE(true, false, false);
+    else return hipErrorInvalidValue;
+#undef AFFINE
     return hipGetLastError();
 }
 

@@ -268,6 +268,11 @@ hipError_t prep_train(clamp_unet* u, hipStream_t st) {
 
 int level_of(int l) { return l < 2 * kLevels ? l / 2 : (4 * kLevels - 1 - l) / 2; }
 
+// Layers whose ReLU pattern masks a backward-data convolution: the first of
+// each block, and the last layer.  Pooling's and the transposed convolutions'
+// backward passes mask the others from the activation, which they read anyway.
+bool has_pattern(int l) { return l % 2 == 0 || l == kConvs - 1; }
+
 // Workspace of a training step: every tensor the backward pass reads.
 struct TrainLayout {
     size_t x8, out, g8, z[kConvs], a[kConvs], bits[kConvs], p[kLevels + 1], s[kLevels], gs[kLevels], G[kLevels][3], gp3;
@@ -290,7 +295,7 @@ TrainLayout train_layout(long nvox) {
     for (int l = 0; l < kConvs; ++l) {
         L.z[l] = take(nv[level_of(l)] * 64);
         L.a[l] = take(nv[level_of(l)] * 64);
-        L.bits[l] = take(nv[level_of(l)] * 4);
+        if (has_pattern(l)) L.bits[l] = take(nv[level_of(l)] * 4);
     }
     for (int k = 1; k <= kLevels; ++k) L.p[k] = take(nv[k] * 64);
     for (int k = 0; k < kLevels; ++k) {
@@ -330,7 +335,7 @@ struct Trainer {
     }
 
     // z = W * in (no bias), batch statistics, a = ReLU(BN(z)) with its ReLU
-    // pattern; updates the running statistics
+    // pattern (has_pattern); updates the running statistics
     hipError_t conv_bn(int l, const uint16_t* in) {
         const int k = level_of(l);
         ConvArgs a = conv(k);
@@ -348,14 +353,15 @@ struct Trainer {
                                            nullptr, nullptr, st);
         if (e == hipSuccess)
             e = clampk::unet_affine(a.out, nullptr, bn(l, 2), nullptr, bn(l, 3), 1, nvox(k), buf<uint16_t>(L.a[l]),
-                                    buf<uint16_t>(L.bits[l]), st);
+                                    has_pattern(l) ? buf<uint16_t>(L.bits[l]) : nullptr, st);
         return e;
     }
 
     // Backward of batch normalisation and convolution l: gy (gradient at the
     // ReLU output, already masked) -> dz -> weight, gamma and beta gradients;
     // the input gradient into gin (masked by the ReLU pattern `mask`, or raw
-    // when NULL; not formed when gin is NULL).
+    // when NULL; not formed when gin is NULL).  in: the layer input; layer 0
+    // reads the float32 volumes x instead (NULL).
     hipError_t conv_bn_back(int l, const uint16_t* gy, uint16_t* dzb, const uint16_t* in, const uint16_t* mask,
                             uint16_t* gin) {
         const int k = level_of(l);
@@ -497,7 +503,7 @@ hipError_t train_step(clamp_unet* u, const float* x, const float* target, int32_
         uint16_t* G2 = B(L.G[k][2]);
         e = clampk::unet_pool_bwd(B(L.a[2 * k + 1]), gcur, B(L.gs[k]), G0, nvol, T.dz[k], T.dy[k], T.dx[k], st);
         if (e == hipSuccess) e = T.conv_bn_back(2 * k + 1, G0, G1, B(L.a[2 * k]), B(L.bits[2 * k]), G2);
-        const uint16_t* in0 = k == 0 ? B(L.x8) : B(L.p[k]);
+        const uint16_t* in0 = k == 0 ? nullptr : B(L.p[k]);
         if (e == hipSuccess) e = T.conv_bn_back(2 * k, G2, G1, in0, nullptr, k == 0 ? nullptr : G0);
         gcur = G0;
     }

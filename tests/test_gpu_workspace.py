@@ -57,3 +57,16 @@ def test_cnn_training_workspace():
     v = 32 * 64 * 64
     per = (C.clamp_cnn_workspace_size(24, 32, 64, 64, True) - C.clamp_cnn_workspace_size(12, 32, 64, 64, True)) / (12 * v)
     assert per <= 16 + 7 * 64 + 7 * 4 + 4 + 16 + 2 * 64 + 0.01
+
+
+def test_unet_training_workspace():
+    """Bytes a voxel of a U-Net training step, level by level: z and the
+    activation of four convolutions, the pooled tensor, skip sum and its
+    gradient, three gradients; and a ReLU pattern for the layers whose
+    backward-data product reads it (three at full resolution, two below)."""
+    from paper_2406_13651_amd import _clamp as C
+    v = 32 * 32 * 128
+    per = (C.clamp_unet_workspace_size(24, 32, 32, 128, True) - C.clamp_unet_workspace_size(12, 32, 32, 128, True)) / (12 * v)
+    levels = 1 + 1 / 8 + 1 / 64
+    want = 16 + 4 + 16 + levels * (4 * 128 + 2 * 64 + 3 * 64) + 64 * (1 / 8 + 1 / 64 + 2 / 512)
+    assert per <= want + 4 * (3 + 2 / 8 + 2 / 64) + 0.01
