@@ -23,10 +23,10 @@ __device__ __forceinline__ float2 cmul(float2 a, float2 b) {
 }
 __device__ __forceinline__ float cabs2(float2 a) { return a.x * a.x + a.y * a.y; }
 
-// a times the twiddle w (its conjugate for S > 0) with the rounding the compiler
-// gives cmul in fft_stages: the products with w.x inside the fused
-// multiply-adds.  Written out where neighbouring butterflies would otherwise
-// be combined into vector code of another rounding.
+// a times the twiddle w (its conjugate for S > 0), the products with w.x inside
+// the fused multiply-adds: written out, so that the rounding is this one in
+// every kernel, also where the compiler would combine neighbouring butterflies
+// into vector code.
 template <int S>
 __device__ __forceinline__ float2 cmul_tw(float2 a, float2 w) {
     if constexpr (S > 0) w.y = -w.y;

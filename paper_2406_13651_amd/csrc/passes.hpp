@@ -376,7 +376,9 @@ __device__ __forceinline__ void row_fft(float2 (&h)[RowIn<NX>::PX], float2* rb, 
 // thread's shares of ||d||^2, sum omega |d|^2 and sum omega |mu|^2.
 // SLICE (the slice pass): |mu|^2 is rounded as the compiler rounds it in the
 // gradient row pass -- the square of x first, in the last sample that of y --
-// so that both report the same sums.
+// so that both report the same sums.  The GPU tests compare a batch, which
+// takes the row pass, with single scenes, which take the slice pass, and fail
+// where a compiler rounds otherwise.
 template <int NX, int TR, bool SLICE = false, int PX, class A>
 __device__ __forceinline__ void row_grad_pointwise(const A& a, float2 (&h)[PX], int t, const float2 (&m)[PX],
                                                    const float (&rp)[PX], float& dd, float& wd, float& wm) {

@@ -1,7 +1,9 @@
 """Batches large enough that each wave of the fused update pass walks every
-look of its rows, against single-scene calls of the same scenes, where up to
-four waves share them and hand r over through the row buffers.  Both add in
-look order with the same operations, so every array of the state is equal bit
+look of its rows (every row length), against single-scene calls of the same
+scenes.  There up to four waves share the looks and hand r over through the
+row buffers, and slices of 32 and 64 points take the one-launch passes, where
+the batch takes the column, row and column passes.  All of them use the same
+float32 operations in the same order, so every array of the state is equal bit
 for bit; the float64 diagnostics differ by the order of their sums at most:
 up to 1e5 positive terms added in runs, below 1e-14 relative."""
 
@@ -15,8 +17,13 @@ ROWS_PER_WAVE = {32: 16, 64: 8, 128: 4, 192: 2, 256: 2, 384: 1, 512: 1}
 
 # nx, ny, nz, looks, radius, with_prior: the last scene alone fills the chip
 SCENES = {
+    32: [(32, 32, 33, 6, 22.7, True), (32, 64, 3, 5, 8.0, True), (32, 512, 26, 2, 8.0, False)],
+    64: [(64, 64, 9, 7, 45.5, True), (64, 32, 5, 3, 15.9, False), (64, 64, 120, 2, 16.0, True)],
+    128: [(128, 64, 3, 4, 16.0, True), (128, 128, 25, 2, 32.0, True)],
     192: [(192, 64, 5, 6, 101.5, True), (192, 192, 8, 3, 48.0, False)],
+    256: [(256, 32, 3, 5, 8.0, True), (256, 128, 13, 2, 32.0, True)],
     384: [(384, 64, 5, 7, 193.0, True), (384, 192, 4, 3, 48.0, False)],
+    512: [(512, 32, 5, 5, 8.0, True), (512, 128, 7, 2, 64.0, False)],
 }
 
 
