@@ -776,26 +776,26 @@ hipError_t agent_launches(const AgentRun& r, const RowArgs& ra, const clampk::Fu
             e = timed(plan, ST_ROW_GRAD, stream, [&] { return clampk::launch_slice_grad(sa, stream); });
         counted(plan, ST_COL_FWD);
     } else {
-    ColArgs ci = col_args(s, L);
-    ci.cmp_in = range ? dfd : resid;
-    ci.band_out = T;
-    ci.part = pci;
-    if (e == hipSuccess)
-        e = timed(plan, ST_COL_INV, stream, [&] { return clampk::launch_col(clampk::COL_INV_COMPACT, ci, stream); });
-    if (e == hipSuccess) {
-        RowArgs g = ra;
-        g.band_in = T;
-        g.band_out = T2;
-        g.part = prow;
-        e = timed(plan, ST_ROW_GRAD, stream, [&] { return clampk::launch_row(clampk::ROW_GRAD, g, stream); });
-    }
-    if (e == hipSuccess) {
-        ColArgs cf = col_args(s, L);
-        cf.band_in = T2;
-        cf.cmp_out = dfd;
-        cf.part = pcf;
-        e = timed(plan, ST_COL_FWD, stream, [&] { return clampk::launch_col(clampk::COL_FWD_COMPACT, cf, stream); });
-    }
+        ColArgs ci = col_args(s, L);
+        ci.cmp_in = range ? dfd : resid;
+        ci.band_out = T;
+        ci.part = pci;
+        if (e == hipSuccess)
+            e = timed(plan, ST_COL_INV, stream, [&] { return clampk::launch_col(clampk::COL_INV_COMPACT, ci, stream); });
+        if (e == hipSuccess) {
+            RowArgs g = ra;
+            g.band_in = T;
+            g.band_out = T2;
+            g.part = prow;
+            e = timed(plan, ST_ROW_GRAD, stream, [&] { return clampk::launch_row(clampk::ROW_GRAD, g, stream); });
+        }
+        if (e == hipSuccess) {
+            ColArgs cf = col_args(s, L);
+            cf.band_in = T2;
+            cf.cmp_out = dfd;
+            cf.part = pcf;
+            e = timed(plan, ST_COL_FWD, stream, [&] { return clampk::launch_col(clampk::COL_FWD_COMPACT, cf, stream); });
+        }
     }
     if (e == hipSuccess && range) {
         clampk::ZArgs za{s.tab, L, dfd, dfd_box, pz_fwd};

@@ -58,11 +58,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
                                                                                               int off) {
     __shared__ float2 tw[NX];
     __shared__ int bpos[NX];
-    __shared__ int bcol[NX];
     __shared__ float2 buf[row_lds_floats2<NX>()];
     __shared__ float ups[64];
     __shared__ float keep[mann_lds_floats<NX>()];
-    const RowLds L{tw, bpos, bcol, buf};
+    const RowLds L{tw, bpos, nullptr, buf};
     const int k = *b.iter;
     const BetaVals bv = beta_vals(b.beta_table[k < b.beta_len ? k : b.beta_len - 1]);
     const BatchItem w = const_ref(b.queue[Q_ROWG] + off + blockIdx.x);

@@ -177,11 +177,10 @@ template <int NX, int MODE, int SPLIT>
 __device__ __forceinline__ void row_upd_mann_block(const RowArgs& a, const FuseArgs& f) {
     __shared__ float2 tw[NX];
     __shared__ int bpos[NX];
-    __shared__ int bcol[NX];
     __shared__ float2 buf[row_lds_floats2<NX>()];
     __shared__ float ups[64];
     __shared__ float keep[mann_lds_floats<NX>()];
-    const RowLds L{tw, bpos, bcol, buf};
+    const RowLds L{tw, bpos, nullptr, buf};
     const BetaVals bv{a.beta, a.inv_beta, a.k_up, a.k_dn};
     row_update_mann<NX, MODE>(a, f, SPLIT, blockIdx.x, gridDim.x, L, bv, ups, keep);
 }
@@ -542,17 +541,20 @@ hipError_t launch_scatter_full(const SceneTables& s, int looks, const float2* cm
     return hipGetLastError();
 }
 
-// Sizes of the slice pass and the LDS a block may take (160 KB per CU, less
-// the reduction's static share).  128-point slices fit as well (70 KB of band
-// and as much for the rows of 16 waves) but leave room for one block per CU,
-// whose passes then wait for each other: 128x128x64 with 9 looks took 194 us
-// an iteration against 187 with the three launches, and 128^3 361 against 352.
+// Sizes of the slice pass, whatever the number of slices and looks: at
+// 64x64x128 with 32 looks, 16 blocks per CU, an iteration takes 333 us with it
+// and 379 with the three launches, at 64x64x16 with 4 looks 42 and 50.  A block
+// with every column in the band takes 73 KB of LDS at most.  128-point slices
+// fit as well (70 KB of band and as much for the rows of 16 waves) but leave
+// room for one block per CU, whose passes then wait for each other:
+// 128x128x64 with 9 looks took 194 us an iteration against 187 with the three
+// launches, and 128^3 361 against 352.
 #define CLAMP_SLICE_SIZES(X) X(32, 32) X(32, 64) X(64, 32) X(64, 64)
-constexpr size_t kSliceLdsMax = 160 * 1024 - 1024;
+static_assert(slice_lds_bytes<64, 64>(64) <= 80 * 1024, "two blocks per CU");
 
 bool slice_path(const SceneTables& s) {
 #define CASE(NX, NY) \
-    if (s.nx == NX && s.ny == NY) return slice_lds_bytes<NX, NY>(s.B) <= kSliceLdsMax;
+    if (s.nx == NX && s.ny == NY) return true;
     CLAMP_SLICE_SIZES(CASE)
 #undef CASE
     return false;

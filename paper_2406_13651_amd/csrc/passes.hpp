@@ -309,7 +309,8 @@ __device__ __forceinline__ int slice_of_row(const T& s, int row) {
 }
 
 // LDS buffers of a row item: twiddles, band position and band column tables
-// (length NX each) and the padded row buffers.
+// (length NX each; the band columns for the passes that write band rows) and
+// the padded row buffers.
 struct RowLds {
     float2* tw;
     int* bpos;
@@ -385,20 +386,18 @@ __device__ __forceinline__ void row_grad_pointwise(const A& a, float2 (&h)[PX], 
 #pragma unroll
     for (int k = 0; k < PX; ++k) {
         const int x = t + k * TR;
-        if (NX % TR == 0 || x < NX) {
-            const float2 ahr = cscale(h[k], a.scale);
-            const float om = 1.f / (rp[k] + a.floor_w);
-            const float2 d = make_float2(ahr.x * a.inv_s2w - om * m[k].x, ahr.y * a.inv_s2w - om * m[k].y);
-            h[k] = d;
-            const float d2 = cabs2(d);
-            dd += d2;
-            wd += om * d2;
-            if constexpr (SLICE) {
-                const float x = k + 1 < PX ? m[k].x : m[k].y, y = k + 1 < PX ? m[k].y : m[k].x;
-                wm = fmaf(om, fmaf(y, y, x * x), wm);
-            } else {
-                wm += om * cabs2(m[k]);
-            }
+        const float2 ahr = cscale(h[k], a.scale);
+        const float om = 1.f / (rp[k] + a.floor_w);
+        const float2 d = make_float2(ahr.x * a.inv_s2w - om * m[k].x, ahr.y * a.inv_s2w - om * m[k].y);
+        h[k] = d;
+        const float d2 = cabs2(d);
+        dd += d2;
+        wd += om * d2;
+        if constexpr (SLICE) {
+            const float x = k + 1 < PX ? m[k].x : m[k].y, y = k + 1 < PX ? m[k].y : m[k].x;
+            wm = fmaf(om, fmaf(y, y, x * x), wm);
+        } else {
+            wm += om * cabs2(m[k]);
         }
     }
 }
@@ -412,7 +411,7 @@ __device__ __forceinline__ void row_item(const A& a, int look, int rgroup, size_
                                          bool load_tables, BetaVals bv) {
     constexpr int TR = row_threads(NX);
     constexpr int RPB = rows_per_block(NX);
-    constexpr int PX = (NX + TR - 1) / TR;          // row samples per thread
+    constexpr int PX = RowIn<NX>::PX;               // row samples per thread
     constexpr int PAD = kRowPad;
     constexpr int RS = lds_len<NX, PAD>();          // padded row length in LDS
     // ROW_UPDATE_EXACT is the update pass with the exact surrogate prox in
@@ -446,15 +445,13 @@ __device__ __forceinline__ void row_item(const A& a, int look, int rgroup, size_
 #pragma unroll
             for (int k = 0; k < PX; ++k) {
                 const int x = t + k * TR;
-                if (NX % TR == 0 || x < NX) {
-                    if constexpr (UPD) {
-                        m[k] = ld_stream(&a.mu[img + x]);
-                        rp[k] = ld_stream(&a.r[img + x]);
-                        wv[k] = ld_stream(&a.w[img + x]);
-                    } else {
-                        m[k] = a.mu[img + x];
-                        rp[k] = a.r[img + x];
-                    }
+                if constexpr (UPD) {
+                    m[k] = ld_stream(&a.mu[img + x]);
+                    rp[k] = ld_stream(&a.r[img + x]);
+                    wv[k] = ld_stream(&a.w[img + x]);
+                } else {
+                    m[k] = a.mu[img + x];
+                    rp[k] = a.r[img + x];
                 }
             }
         }
@@ -528,18 +525,16 @@ __device__ __forceinline__ void row_item(const A& a, int look, int rgroup, size_
 #pragma unroll
             for (int k = 0; k < PX; ++k) {
                 const int x = t + k * TR;
-                if (NX % TR == 0 || x < NX) {
-                    const float2 ahr = cscale(h[k], a.scale);
-                    const float r0 = rp[k];
-                    const float v = wv[k];
-                    const float om = 1.f / (r0 + a.floor_w);
-                    const float2 d = make_float2(ahr.x * a.inv_s2w - om * m[k].x, ahr.y * a.inv_s2w - om * m[k].y);
-                    const float2 m1 = make_float2(m[k].x + gamma * d.x, m[k].y + gamma * d.y);
-                    st_stream(&a.mu[img + x], m1);
-                    const float rn = r_update_voxel<MODE>(a, bv, r0, v, m1, fb);
-                    st_stream(&a.r[img + x], rn);
-                    wm1 += om * cabs2(m1);
-                }
+                const float2 ahr = cscale(h[k], a.scale);
+                const float r0 = rp[k];
+                const float v = wv[k];
+                const float om = 1.f / (r0 + a.floor_w);
+                const float2 d = make_float2(ahr.x * a.inv_s2w - om * m[k].x, ahr.y * a.inv_s2w - om * m[k].y);
+                const float2 m1 = make_float2(m[k].x + gamma * d.x, m[k].y + gamma * d.y);
+                st_stream(&a.mu[img + x], m1);
+                const float rn = r_update_voxel<MODE>(a, bv, r0, v, m1, fb);
+                st_stream(&a.r[img + x], rn);
+                wm1 += om * cabs2(m1);
             }
         }
         wave_or_fault(fb, a.fault);
@@ -569,7 +564,7 @@ __device__ __forceinline__ void row_item(const A& a, int look, int rgroup, size_
 // Partial sums per block: sum omega |mu'|^2 of each look into a.part, the convergence error's (sum_j (r_j - w_bar)^2, N w_bar^2) into f.part.
 template <int NX>
 __host__ __device__ constexpr int mann_lds_floats() {
-    return 2 * kBlock * ((NX + row_threads(NX) - 1) / row_threads(NX));
+    return 2 * kBlock * RowIn<NX>::PX;
 }
 
 // LDS: ups[64] holds the agent weights, keep[mann_lds_floats<NX>()] each
@@ -582,7 +577,7 @@ __device__ __forceinline__ void row_update_mann(const A& a, const F& f, int spli
     __shared__ double wsum[64][4];                  // [look][wave], at most 64 looks
     constexpr int TR = row_threads(NX);
     constexpr int RPW = 64 / TR;                    // rows per wave
-    constexpr int PX = (NX + TR - 1) / TR;
+    constexpr int PX = RowIn<NX>::PX;
     constexpr int PAD = kRowPad;
     constexpr int RS = lds_len<NX, PAD>();
     // 512-point rows: one barrier per look keeps the block's four rows on the
@@ -606,8 +601,6 @@ __device__ __forceinline__ void row_update_mann(const A& a, const F& f, int spli
     for (int i = tid; i < NX; i += kBlock) {
         L.tw[i] = s.tw_x[i];
         L.bpos[i] = s.band_pos[i];
-        const int bc = s.band_cols[i < s.B ? i : 0];
-        L.bcol[i] = i < s.B ? bc : 0;
     }
     // the agent weights go to LDS with constant indices: indexing the
     // argument block by the look would make a private copy of it
@@ -622,13 +615,12 @@ __device__ __forceinline__ void row_update_mann(const A& a, const F& f, int spli
 #pragma unroll
     for (int k = 0; k < PX; ++k) sr[k] = e2[k] = 0.f;
     if (part == 0) {
-        // all loads issued before the first is used (samples past the row
-        // end and inactive rows read the row's first sample)
+        // all loads issued before the first is used (inactive rows read row 0)
         float a0[PX], a1[PX];
 #pragma unroll
         for (int k = 0; k < PX; ++k) {
             const int x = t + k * TR;
-            const size_t i = pix + ((NX % TR == 0 || x < NX) ? x : 0);
+            const size_t i = pix + x;
             a0[k] = ld_stream(f.xbar + i);
             a1[k] = ld_stream(f.wbar + i);
         }
@@ -669,11 +661,9 @@ __device__ __forceinline__ void row_update_mann(const A& a, const F& f, int spli
 #pragma unroll
                 for (int k = 0; k < PX; ++k) {
                     const int x = t + k * TR;
-                    if (NX % TR == 0 || x < NX) {
-                        m[k] = ld_stream(&a.mu[img + x]);
-                        rp[k] = ld_stream(&a.r[img + x]);
-                        uv[k] = ld_stream(&f.u[img + x]);
-                    }
+                    m[k] = ld_stream(&a.mu[img + x]);
+                    rp[k] = ld_stream(&a.r[img + x]);
+                    uv[k] = ld_stream(&f.u[img + x]);
                 }
             }
             const float gamma = (float)a.diag[(size_t)l * kDiag];
@@ -683,28 +673,26 @@ __device__ __forceinline__ void row_update_mann(const A& a, const F& f, int spli
 #pragma unroll
                 for (int k = 0; k < PX; ++k) {
                     const int x = t + k * TR;
-                    if (NX % TR == 0 || x < NX) {
-                        const float2 ahr = cscale(h[k], a.scale);
-                        const float r0 = rp[k];
-                        const float om = 1.f / (r0 + a.floor_w);
-                        const float2 d = make_float2(ahr.x * a.inv_s2w - om * m[k].x, ahr.y * a.inv_s2w - om * m[k].y);
-                        const float2 m1 = make_float2(m[k].x + gamma * d.x, m[k].y + gamma * d.y);
-                        st_stream(&a.mu[img + x], m1);
-                        const float v = uv[k] + f.two_rho * xo[k * kst + kl];
-                        const float rn = r_update_voxel<MODE>(a, bv, r0, v, m1, fb);
-                        st_stream(&a.r[img + x], rn);
-                        st_stream(&f.u[img + x], v - f.two_rho * rn);
-                        if (split == 1) {
-                            sr[k] = fmaf(ul, rn, sr[k]);
-                            const float e = rn - wb[k * kst + kl];
-                            e2[k] = fmaf(e, e, e2[k]);
-                        } else {
-                            // over elements that other lanes of the wave took the transform's
-                            // last inputs from: the transform synchronised after reading them
-                            rx[k * 64 + lane] = rn;
-                        }
-                        wm1 += om * cabs2(m1);
+                    const float2 ahr = cscale(h[k], a.scale);
+                    const float r0 = rp[k];
+                    const float om = 1.f / (r0 + a.floor_w);
+                    const float2 d = make_float2(ahr.x * a.inv_s2w - om * m[k].x, ahr.y * a.inv_s2w - om * m[k].y);
+                    const float2 m1 = make_float2(m[k].x + gamma * d.x, m[k].y + gamma * d.y);
+                    st_stream(&a.mu[img + x], m1);
+                    const float v = uv[k] + f.two_rho * xo[k * kst + kl];
+                    const float rn = r_update_voxel<MODE>(a, bv, r0, v, m1, fb);
+                    st_stream(&a.r[img + x], rn);
+                    st_stream(&f.u[img + x], v - f.two_rho * rn);
+                    if (split == 1) {
+                        sr[k] = fmaf(ul, rn, sr[k]);
+                        const float e = rn - wb[k * kst + kl];
+                        e2[k] = fmaf(e, e, e2[k]);
+                    } else {
+                        // over elements that other lanes of the wave took the transform's
+                        // last inputs from: the transform synchronised after reading them
+                        rx[k * 64 + lane] = rn;
                     }
+                    wm1 += om * cabs2(m1);
                 }
             }
             // the wave's share of the look's sum omega |mu'|^2 (no wait for the
@@ -753,7 +741,7 @@ __device__ __forceinline__ void row_update_mann(const A& a, const F& f, int spli
         for (int k = 0; k < PX; ++k) {
             if ((k & (split - 1)) != part) continue;
             const int x = t + k * TR;
-            const size_t i = pix + ((NX % TR == 0 || x < NX) ? x : 0);
+            const size_t i = pix + x;
             rpv[k] = rsrc[i];
             wpv[k] = ld_stream(wsrc + i);
         }
@@ -763,18 +751,16 @@ __device__ __forceinline__ void row_update_mann(const A& a, const F& f, int spli
         for (int k = 0; k < PX; ++k) {
             if ((k & (split - 1)) != part) continue;
             const int x = t + k * TR;
-            if (NX % TR == 0 || x < NX) {
-                const float wbk = wb[k * kst + kl];
-                const float e = rpv[k] - wbk;
-                const float s_r = prior ? sr[k] + up * rpv[k] : sr[k];
-                const float nm = e2[k] + (prior ? e * e : 0.f);
-                const float xb = 2.f * s_r - wbk;
-                if (prior) st_stream(f.wprior + pix + x, wpv[k] + f.two_rho * (xb - rpv[k]));
-                st_stream(f.xbar + pix + x, xb);
-                st_stream(f.wbar + pix + x, wbk + f.two_rho * (s_r - wbk));
-                num += (double)nm;
-                den += (double)N * ((double)wbk * wbk);
-            }
+            const float wbk = wb[k * kst + kl];
+            const float e = rpv[k] - wbk;
+            const float s_r = prior ? sr[k] + up * rpv[k] : sr[k];
+            const float nm = e2[k] + (prior ? e * e : 0.f);
+            const float xb = 2.f * s_r - wbk;
+            if (prior) st_stream(f.wprior + pix + x, wpv[k] + f.two_rho * (xb - rpv[k]));
+            st_stream(f.xbar + pix + x, xb);
+            st_stream(f.wbar + pix + x, wbk + f.two_rho * (s_r - wbk));
+            num += (double)nm;
+            den += (double)N * ((double)wbk * wbk);
         }
     }
     wave_or_fault(fb, a.fault);
@@ -1013,7 +999,7 @@ struct SliceGeo {
 // that the 64 / TY columns of TY consecutive rows spread over the LDS banks;
 // every eighth row shifts by as much again, for the autosort stores, whose
 // rows are eight apart.
-__host__ __device__ inline int slice_stride(int cpw, int B) {
+__host__ __device__ constexpr int slice_stride(int cpw, int B) {
     const int m = (B + cpw - 1) / cpw;
     return cpw * (m | 1);
 }
@@ -1024,7 +1010,7 @@ __host__ __device__ constexpr int slice_pos(int y, int b, int stride, int cpw) {
 // Dynamic LDS of the slice pass in bytes: S, the waves' row buffers, the two
 // twiddle tables, the band column tables.
 template <int NX, int NY>
-__host__ __device__ inline size_t slice_lds_bytes(int B) {
+__host__ __device__ constexpr size_t slice_lds_bytes(int B) {
     using G = SliceGeo<NX, NY>;
     const int st = slice_stride(G::CPW, B);
     return ((size_t)slice_pos(NY - 1, 0, st, G::CPW) + st + (size_t)G::NW * G::RPW * G::RS + NX + NY) * sizeof(float2) +
