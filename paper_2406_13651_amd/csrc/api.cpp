@@ -1200,8 +1200,8 @@ clamp_status clamp_batch_create(const clamp_plan* plan, const clamp_batch_scene*
         return fail(CLAMP_EINVAL, "either every scene of a batch has an xbar (the fused Mann step) or none has");
     const bool fused = n_fused == ns && ns > 0;
     // the fused update pass of one row length is one launch over its scenes:
-    // four waves share a row group's looks (mann_split) where that launch
-    // still fits on the chip at once, else each wave walks every look
+    // four waves share a row group's looks where that launch holds three
+    // blocks per CU at most (mann_split), else each wave walks every look
     long blocks4[kSizeClasses] = {};
     for (const Scene& s : plan->scenes) blocks4[length_class(s.sc.nx)] += mann_blocks(s.tab, 4);
     // voxels that the Gaussian prior's launches of 64- and 32-voxel tiles smooth

@@ -51,8 +51,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(!PERSIST
 }
 
 // The update pass with the Mann step fused in, one block per item (scene,
-// block of the scene) of the segment starting at `off` (row_update_mann); three waves per SIMD, as the single-scene
-// kernel.
+// block of the scene) of the segment starting at `off` (row_update_mann); at
+// least three waves per SIMD, as the single-scene kernel.
 template <int NX, int SPLIT>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) void kb_row_mann(BatchLaunch b,
                                                                                               int off) {

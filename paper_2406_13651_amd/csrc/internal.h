@@ -175,12 +175,12 @@ struct SliceArgs {
 bool slice_path(const SceneTables& s);  // whether launch_slice_grad takes this scene
 hipError_t launch_slice_grad(const SliceArgs& a, hipStream_t st);
 
-// The Mann step fused into the update pass (one block walks every look of
-// its rows).  The forward agents' Mann state is kept as u_l = w_l - 2 rho
-// xbar with xbar the reflected average x_bar of the previous step, so that
-// the pass never re-reads a look: it forms v = u_l + 2 rho xbar_old, writes
-// u_l' = v - 2 rho r_l, and after the last look xbar_new, w_bar and the prior
-// agent's w (kept whole).
+// The Mann step fused into the update pass (one wave walks every look of a
+// group of rows, or two or four waves share them).  The forward agents' Mann
+// state is kept as u_l = w_l - 2 rho xbar with xbar the reflected average x_bar
+// of the previous step, so that the pass never re-reads a look: it forms v =
+// u_l + 2 rho xbar_old, writes u_l' = v - 2 rho r_l, and after the last look
+// xbar_new, w_bar and the prior agent's w (kept whole).
 struct FuseArgs {
     float* u;             // [looks][n] in: u_l, out: u_l'
     float* wprior;        // [n] the prior agent's w, in and out (NULL without a prior)

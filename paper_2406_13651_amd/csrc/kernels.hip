@@ -167,10 +167,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) voi
     row_item<NX, ROW_GRAD>(a, blockIdx.y, blockIdx.x, (size_t)blockIdx.y * gridDim.x + blockIdx.x, L, true, bv);
 }
 
-// The update pass with the Mann step fused in (row_update_mann).  Held to three waves per SIMD (168
-// registers): the per-voxel sums across looks come on top of the update
-// pass's registers, and at four waves (128) the compiler spills 25 of them
-// to scratch inside the look loop.
+// The update pass with the Mann step fused in (row_update_mann).  Held to at
+// least three waves per SIMD (168 registers).  Rows of 32 to 192 and of 384
+// points need 128 registers or fewer and run four.  The 256-point rows need 136
+// and would spill seven of them to scratch inside the look loop at four; the
+// 512-point rows need 131, and their LDS (42 KB) holds three blocks per CU.
 // SPLIT waves share a row group's looks; a compile-time number, as a run-time
 // one cost the 512-point rows 26 spilled scalar registers.
 template <int NX, int MODE, int SPLIT>
@@ -409,11 +410,15 @@ __global__ __launch_bounds__(kBlock) void k_gauss3d(PriorArgs p) {
 #define CLAMP_SIZES(X) X(32) X(64) X(128) X(192) X(256) X(384) X(512)
 
 // Waves sharing a row group's looks in the fused update pass: as many of a
-// block's four as there are looks for, while the grid still fits on the chip
-// at once (three blocks per CU).  Past that the sharing only spreads a block's
-// accesses over more streams: 256x256x64 with 16 looks took 1040 us an
-// iteration with four waves per group against 957 with one; 64x64x32 with 8
-// looks went from 82 us to 54 with the sharing and the joined final sums.
+// block's four as there are looks for, while the grid holds three blocks per CU
+// at most.  Past that the sharing only spreads a block's accesses over more
+// streams: 256x256x64 with 16 looks took 1040 us an iteration with four waves
+// per group against 957 with one; 64x64x32 with 8 looks went from 82 us to 54
+// with the sharing and the joined final sums.  (The kernels of 256 and 512
+// points fit three blocks per CU, the others four.  Sharing up to four blocks
+// per CU, at 3.2 to 3.8: 32x512x26 with 8 looks 190 -> 204 us an iteration,
+// 64x64x112 with 12 141 -> 152, 128x128x28 with 9 100 -> 101; but 192x192x9
+// with 8 looks 80 -> 77 and 384x192x5 with 8 80 -> 77.5.)
 int mann_split(const SceneTables& s, int looks, int cus) {
     int split = 1;
     while (split < 4 && 2 * split <= looks && mann_blocks(s, 2 * split) <= 3 * cus) split *= 2;

@@ -1060,7 +1060,7 @@ __device__ __forceinline__ void slice_grad_item(const A& a, int zl, float2* lds)
     }
     for (int i = tid; i < NY; i += NT) twy[i] = s.tw_y[i];
 
-    // columns: lane (ct, cc) holds rows ct + 8 k' of column g CPW + cc
+    // columns: lane (ct, cc) holds rows ct + k TY of column g CPW + cc
     const int cc = lane % CPW, ct = lane / CPW;
     const float2* src = a.cmp_in + (size_t)zl * s.P;
     double r2 = 0.0;

@@ -148,8 +148,8 @@ __global__ __launch_bounds__(kBlock) void k_l21_shrink(int per, int chunks, floa
 // the plane that is overwritten next has passed it.
 // Bound by memory (the images of a 256x256x64 volume stay in the 256 MB
 // Infinity Cache): 28 bytes per voxel and step where separate divergence and
-// projection passes move 48.  20 steps at 256x256x64: 410 us (5.9 TB/s of
-// those bytes) against 940 us for the two passes; with the tiles dealt to the
+// projection passes move 48.  20 steps at 256x256x64: 410 us (5.6 TB/s of
+// those bytes; the first step reads no p) against 940 us for the two passes; with the tiles dealt to the
 // XCDs one by one instead of in runs, the halos of tiles on other XCDs made
 // it 118 MB read per step instead of 67, and 523 us.
 template <int LX, bool ZERO>
