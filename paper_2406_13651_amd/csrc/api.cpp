@@ -879,6 +879,7 @@ clamp_status clamp_fwd_agent_mace(const clamp_plan* plan, int32_t scene, const c
     f.two_rho = 2.f * params->rho;
     f.n_agents = params->n_agents;
     f.split = params->r_update == CLAMP_R_EXACT ? 1 : clampk::mann_split(s.tab, L, plan->cus);
+    f.lockstep = clampk::mann_lockstep(s.sc.nx, clampk::row_groups(s.tab), plan->cus);
     const int mode = params->r_update == CLAMP_R_EXACT ? clampk::ROW_UPDATE_EXACT : clampk::ROW_UPDATE;
     hipError_t e = agent_launches(run, agent_row_args(run, w), &f, conv_err, [&](const RowArgs& u) {
         return timed(plan, ST_ROW_UPDATE_MANN, run.stream,
@@ -1200,10 +1201,9 @@ clamp_status clamp_batch_create(const clamp_plan* plan, const clamp_batch_scene*
         return fail(CLAMP_EINVAL, "either every scene of a batch has an xbar (the fused Mann step) or none has");
     const bool fused = n_fused == ns && ns > 0;
     // the fused update pass of one row length is one launch over its scenes:
-    // four waves share a row group's looks where that launch holds three
-    // blocks per CU at most (mann_split), else each wave walks every look
-    long blocks4[kSizeClasses] = {};
-    for (const Scene& s : plan->scenes) blocks4[length_class(s.sc.nx)] += mann_blocks(s.tab, 4);
+    // the row groups of all of them decide how many waves share a group's looks
+    long groups[kSizeClasses] = {};
+    for (const Scene& s : plan->scenes) groups[length_class(s.sc.nx)] += row_groups(s.tab);
     // voxels that the Gaussian prior's launches of 64- and 32-voxel tiles smooth
     size_t prior_voxels[2] = {0, 0};
     for (int i = 0; i < ns; ++i)
@@ -1214,7 +1214,7 @@ clamp_status clamp_batch_create(const clamp_plan* plan, const clamp_batch_scene*
     for (int i = 0; i < ns; ++i) {
         const Scene& s = plan->scenes[i];
         const clamp_batch_scene& bs = scenes[i];
-        const int split = blocks4[length_class(s.sc.nx)] <= 3 * plan->cus ? 4 : 1;
+        const int split = batch_mann_split(s.sc.nx, groups[length_class(s.sc.nx)], plan->cus);
         if ((st = check_params(s, &bs.params, true)) != CLAMP_OK) return fail(st, "scene %d: %s", i, g_err.c_str());
         if (bs.params.n_agents > 40) return fail(CLAMP_EUNSUPPORTED, "scene %d: a batch holds at most 40 agents", i);
         if (bs.params.r_update != CLAMP_R_QUADRATIC)
@@ -1291,6 +1291,7 @@ clamp_status clamp_batch_create(const clamp_plan* plan, const clamp_batch_scene*
             f.two_rho = m.two_rho;
             f.n_agents = m.n_agents;
             f.split = split;
+            f.lockstep = mann_lockstep(s.sc.nx, groups[length_class(s.sc.nx)], plan->cus);
             sb.fuse = f;
         }
         sb.with_prior = with_prior ? 1 : 0;
@@ -1347,7 +1348,7 @@ clamp_status clamp_batch_create(const clamp_plan* plan, const clamp_batch_scene*
             if (by[k].empty()) continue;
             const int g = L.nseg[side]++;
             L.seg_len[side][g] = kLengths[k];
-            if (side == 2) L.mann_split[g] = blocks4[k] <= 3 * plan->cus ? 4 : 1;
+            if (side == 2) L.mann_split[g] = batch_mann_split(kLengths[k], groups[k], plan->cus);
             L.seg_off[side][g] = (int)dst.size();
             L.seg_count[side][g] = (int)by[k].size();
             dst.insert(dst.end(), by[k].begin(), by[k].end());

@@ -192,8 +192,12 @@ struct FuseArgs {
     float two_rho;
     int n_agents;
     int split;            // waves that share a row group's looks: 1, 2 or 4 (mann_split; exact prox: 1)
+    int lockstep;         // 64-point rows, split 1: a block's waves stay on the same look (mann_lockstep)
 };
 int mann_split(const SceneTables& s, int looks, int cus);
+// The same for a batch's launch over all scenes of one row length: 4 or 1.
+int batch_mann_split(int nx, long groups, int cus);
+bool mann_lockstep(int nx, long groups, int cus);
 hipError_t launch_col(int mode, const ColArgs& a, hipStream_t st);
 hipError_t launch_row(int mode, const RowArgs& a, hipStream_t st);
 // mode ROW_UPDATE or ROW_UPDATE_EXACT; a.w is unused (the fused pass forms v

@@ -409,21 +409,48 @@ __global__ __launch_bounds__(kBlock) void k_gauss3d(PriorArgs p) {
 // Launchers
 #define CLAMP_SIZES(X) X(32) X(64) X(128) X(192) X(256) X(384) X(512)
 
-// Waves sharing a row group's looks in the fused update pass: as many of a
-// block's four as there are looks for, while the grid holds three blocks per CU
-// at most.  Past that the sharing only spreads a block's accesses over more
-// streams: 256x256x64 with 16 looks took 1040 us an iteration with four waves
-// per group against 957 with one; 64x64x32 with 8 looks went from 82 us to 54
-// with the sharing and the joined final sums.  (The kernels of 256 and 512
-// points fit three blocks per CU, the others four.  Sharing up to four blocks
-// per CU, at 3.2 to 3.8: 32x512x26 with 8 looks 190 -> 204 us an iteration,
-// 64x64x112 with 12 141 -> 152, 128x128x28 with 9 100 -> 101; but 192x192x9
-// with 8 looks 80 -> 77 and 384x192x5 with 8 80 -> 77.5.)
-int mann_split(const SceneTables& s, int looks, int cus) {
-    int split = 1;
-    while (split < 4 && 2 * split <= looks && mann_blocks(s, 2 * split) <= 3 * cus) split *= 2;
-    return split;
+// Up to how many row groups (the rows of one wave) `split` waves share a
+// group's looks in the fused update pass.  The sharing shortens the serial
+// chain over the looks while waves are few; it costs two barriers and an
+// exchange of r a turn, and spreads a block's accesses over more streams.
+// Update pass in us with one, two and four waves, at 256, 512, 768, 1024 and
+// 1536 groups (dashes: not a choice of the rule):
+//   32 points,  4 looks: 22 21 17, 30 37 38, 42 54 60, 60 73 74, 106 118 121
+//   32 points,  8 looks: 45 40 32, 69 59 72, 89 101 111, 116 131 135
+//   64 points,  2 looks: 13 11 -, 14 13 -, 16 18 -, 17 21 -, 29 33 -
+//   64 points,  8 looks: 37 29 19, 44 33 31, 48 50 47, 54 57 67, 94 90 97
+//   128 points, 8 looks: 37 25 17, 40 29 23, 43 36 30, 44 37 39, 62 52 59
+//   256 points, 2 looks: 13 10 -, 14 12 -, 14 14 -, 15 17 to 21 -, 19 20 -
+//   256 points, 8 looks: 32 24 16, 37 26 22, 38 33 27, 41 35 39, 50 45 50
+//   512 points, 2 looks: 13 11 -, 14 12 -, 15 15 -, 16 17 to 20 -, 20 20 -
+// Longer rows gain like 128 points; two looks of 192 and 384 points gain up
+// to 1536 groups.  Grids past those lose with any sharing: 256x256x64 with 16
+// looks took 1040 us an iteration with four waves against 957 with one.
+static int mann_groups(int nx, int looks, int split, int cus) {
+    if (split == 4) return nx == 32 ? cus : 3 * cus;
+    if (nx == 32) return looks >= 8 ? 2 * cus : cus;
+    if (looks >= 4) return 6 * cus;
+    return nx == 64 ? 2 * cus : nx == 256 || nx == 512 ? 3 * cus : 6 * cus;
 }
+
+int mann_split(const SceneTables& s, int looks, int cus) {
+    const int groups = row_groups(s);
+    for (int split = 4; split > 1; split /= 2)
+        if (looks >= split && groups <= mann_groups(s.nx, looks, split, cus)) return split;
+    return 1;
+}
+
+int batch_mann_split(int nx, long groups, int cus) { return groups <= mann_groups(nx, 0, 4, cus) ? 4 : 1; }
+
+// Whether the four waves of a block stay on the same look, one barrier a look,
+// where each walks all of them: 64-point rows past one block per CU (update
+// pass with 8 looks at 2048 groups 107 us with it and 112 without, at 8192
+// 570 and 585; at 1024, one block per CU, 59 and 54).  Rows of 32 and 512
+// points always do (32 points, 16 looks at 1024 groups: 213 and 224;
+// 512x512x64 with 8 looks: 1039 us an iteration and 1048); rows of 128 to 384
+// points run their waves apart (128^3 with 9 looks: 353 us an iteration, 356
+// with the barrier).
+bool mann_lockstep(int nx, long groups, int cus) { return nx == 64 && groups > 4L * cus; }
 
 static int g_col_grid_cap = 0;
 

@@ -580,10 +580,6 @@ __device__ __forceinline__ void row_update_mann(const A& a, const F& f, int spli
     constexpr int PX = RowIn<NX>::PX;
     constexpr int PAD = kRowPad;
     constexpr int RS = lds_len<NX, PAD>();
-    // 512-point rows: one barrier per look keeps the block's four rows on the
-    // same look (512x512x64, 8 looks: 1039 us with it, 1048 without); shorter
-    // rows run the waves apart (128^3, 9 looks: 353 us an iteration against 356)
-    constexpr bool kLockstep = NX >= 512;
     const auto& s = a.s;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -699,7 +695,7 @@ __device__ __forceinline__ void row_update_mann(const A& a, const F& f, int spli
             // other waves here)
             const double acc = wave_sums_f64<1>({(double)wm1});
             if (lane == 0) wsum[l][wave] = acc;
-            if (kLockstep && split == 1) __syncthreads();
+            if (split == 1 && (NX == 32 || NX == 512 || (NX == 64 && f.lockstep))) __syncthreads();
         }
         if (split > 1) {
             __syncthreads();

@@ -17,7 +17,8 @@ ROWS_PER_WAVE = {32: 16, 64: 8, 128: 4, 192: 2, 256: 2, 384: 1, 512: 1}
 
 # nx, ny, nz, looks, radius, with_prior: the last scene alone fills the chip
 SCENES = {
-    32: [(32, 32, 33, 6, 22.7, True), (32, 64, 3, 5, 8.0, True), (32, 512, 26, 2, 8.0, False)],
+    32: [(32, 32, 33, 6, 22.7, True), (32, 64, 3, 5, 8.0, True), (32, 512, 12, 9, 8.0, True),
+         (32, 512, 26, 2, 8.0, False)],
     64: [(64, 64, 9, 7, 45.5, True), (64, 32, 5, 3, 15.9, False), (64, 64, 120, 2, 16.0, True)],
     128: [(128, 64, 3, 4, 16.0, True), (128, 128, 25, 2, 32.0, True)],
     192: [(192, 64, 5, 6, 101.5, True), (192, 192, 8, 3, 48.0, False)],
