@@ -210,11 +210,18 @@ __global__ __launch_bounds__((SliceGeo<NX, NY>::NT)) void k_slice_grad(SliceArgs
 // Four samples of one slice per thread, kBlock apart: a slice holds a multiple
 // of 1024 samples (transform lengths are multiples of 32), so a block lies in
 // one slice and its loads are in flight together (64x64x32, 16 looks, 17 MB
-// written: 5.9 us; one sample per thread with a 64-bit division took 8.3).
+// written: 6.0 us; one sample per thread with a 64-bit division took 8.2).
+// Blocks go to the eight XCDs in turn and get runs of neighbouring chunks per
+// XCD: the compact layout is column by column, so the 16 rows of a slice that
+// share a 128-byte line are read through one L2.  512x512x16, 4 looks, 134 MB
+// written: 27 us; dealt to the XCDs chunk by chunk, two rows each, 43 us, and
+// one sample per thread, half a row a block, 35 us.
 constexpr int kScatterPer = 4;
 __global__ __launch_bounds__(kBlock) void k_scatter_full(SceneTables s, int chunks, const float2* cmp, float2* full) {
-    const unsigned zl = blockIdx.x / (unsigned)chunks;
-    const unsigned pos = (blockIdx.x - zl * (unsigned)chunks) * (kScatterPer * kBlock) + threadIdx.x;
+    const unsigned per_xcd = gridDim.x / 8u;
+    const unsigned blk = blockIdx.x < 8u * per_xcd ? (blockIdx.x % 8u) * per_xcd + blockIdx.x / 8u : blockIdx.x;
+    const unsigned zl = blk / (unsigned)chunks;
+    const unsigned pos = (blk - zl * (unsigned)chunks) * (kScatterPer * kBlock) + threadIdx.x;
     const float2* src = cmp + (size_t)zl * s.P;
     float2* dst = full + (size_t)zl * s.ny * s.nx;
     int p[kScatterPer];
