@@ -459,9 +459,11 @@ __device__ __forceinline__ void row_item(const A& a, int look, int rgroup, size_
     __syncthreads();  // the previous item's readers of the LDS buffers are done
     if (load_tables) {
         for (int i = tid; i < NX; i += kBlock) {
-            L.tw[i] = s.tw_x[i];
-            L.bpos[i] = s.band_pos[i];
-            const int bc = s.band_cols[i < s.B ? i : 0];  // unconditional: one wait for all three tables
+            // unconditional, and before the first store: one wait for all three tables
+            const float2 w = s.tw_x[i];
+            const int bp = s.band_pos[i], bc = s.band_cols[i < s.B ? i : 0];
+            L.tw[i] = w;
+            L.bpos[i] = bp;
             L.bcol[i] = i < s.B ? bc : 0;
         }
         __syncthreads();
@@ -474,9 +476,14 @@ __device__ __forceinline__ void row_item(const A& a, int look, int rgroup, size_
     float2 in[In::kCount], h[PX];
     const bool has = active && In::has(t);
     if constexpr (MODE == ROW_FWD) {
+        // all loads issued before the first is used (threads without samples
+        // read the row's first ones, inactive rows row 0)
+        const float2* row_in = a.img_in + img + (In::has(t) ? t : 0);
+#pragma unroll
+        for (int q = 0; q < In::kCount; ++q) in[q] = row_in[q * In::kStep];
 #pragma unroll
         for (int q = 0; q < In::kCount; ++q)
-            in[q] = has ? a.img_in[img + t + q * In::kStep] : make_float2(0.f, 0.f);
+            if (!has) in[q] = make_float2(0.f, 0.f);
     } else {
         // The row's band samples: all loads are issued before the first
         // is used (samples off the band read the row's first band sample and
