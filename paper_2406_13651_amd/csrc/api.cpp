@@ -1348,7 +1348,10 @@ clamp_status clamp_batch_create(const clamp_plan* plan, const clamp_batch_scene*
             if (by[k].empty()) continue;
             const int g = L.nseg[side]++;
             L.seg_len[side][g] = kLengths[k];
-            if (side == 2) L.mann_split[g] = batch_mann_split(kLengths[k], groups[k], plan->cus);
+            if (side == 2) {
+                L.mann_split[g] = batch_mann_split(kLengths[k], groups[k], plan->cus);
+                L.mann_pad[g] = mann_lds_pad(kLengths[k], mann_lockstep(kLengths[k], groups[k], plan->cus));
+            }
             L.seg_off[side][g] = (int)dst.size();
             L.seg_count[side][g] = (int)by[k].size();
             dst.insert(dst.end(), by[k].begin(), by[k].end());

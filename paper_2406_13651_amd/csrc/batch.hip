@@ -236,7 +236,7 @@ static void launch_rowg_segments(const BatchLaunch& b, hipStream_t st) {
 #define CASE(N)                                                                            \
     case N:                                                                                \
         if (b.mann_split[g] == 1)                                                          \
-            hipLaunchKernelGGL((kb_row_mann<N, 1>), dim3(cnt), dim3(kBlock), 0, st, b, off); \
+            hipLaunchKernelGGL((kb_row_mann<N, 1>), dim3(cnt), dim3(kBlock), b.mann_pad[g], st, b, off); \
         else                                                                               \
             hipLaunchKernelGGL((kb_row_mann<N, 4>), dim3(cnt), dim3(kBlock), 0, st, b, off); \
         break;

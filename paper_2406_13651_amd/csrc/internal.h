@@ -192,12 +192,13 @@ struct FuseArgs {
     float two_rho;
     int n_agents;
     int split;            // waves that share a row group's looks: 1, 2 or 4 (mann_split; exact prox: 1)
-    int lockstep;         // 64-point rows, split 1: a block's waves stay on the same look (mann_lockstep)
+    int lockstep;         // 64- and 128-point rows, split 1: a block's waves stay on the same look (mann_lockstep)
 };
 int mann_split(const SceneTables& s, int looks, int cus);
 // The same for a batch's launch over all scenes of one row length: 4 or 1.
 int batch_mann_split(int nx, long groups, int cus);
 bool mann_lockstep(int nx, long groups, int cus);
+unsigned mann_lds_pad(int nx, bool lockstep);  // dynamic LDS of the fused update pass, split 1
 hipError_t launch_col(int mode, const ColArgs& a, hipStream_t st);
 hipError_t launch_row(int mode, const RowArgs& a, hipStream_t st);
 // mode ROW_UPDATE or ROW_UPDATE_EXACT; a.w is unused (the fused pass forms v
@@ -358,6 +359,7 @@ struct BatchLaunch {
     int seg_grid[3][kSizeClasses];
     int nseg[3];
     int mann_split[kSizeClasses];  // waves per row group in a segment of the fused update pass (1 or 4)
+    unsigned mann_pad[kSizeClasses];  // its dynamic LDS (mann_lds_pad)
     int gauss_cz[2];            // range slices of a tile in Q_PRIOR64 and Q_PRIOR32 (gauss_slices)
     const float* beta_table;    // device [beta_len]
     int beta_len;

@@ -449,15 +449,21 @@ int mann_split(const SceneTables& s, int looks, int cus) {
 
 int batch_mann_split(int nx, long groups, int cus) { return groups <= mann_groups(nx, 0, 4, cus) ? 4 : 1; }
 
-// Whether the four waves of a block stay on the same look, one barrier a look,
-// where each walks all of them: 64-point rows past one block per CU (update
-// pass with 8 looks at 2048 groups 107 us with it and 112 without, at 8192
-// 570 and 585; at 1024, one block per CU, 59 and 54).  Rows of 32 and 512
-// points always do (32 points, 16 looks at 1024 groups: 213 and 224;
-// 512x512x64 with 8 looks: 1039 us an iteration and 1048); rows of 128 to 384
-// points run their waves apart (128^3 with 9 looks: 353 us an iteration, 356
-// with the barrier).
-bool mann_lockstep(int nx, long groups, int cus) { return nx == 64 && groups > 4L * cus; }
+// Whether the four waves of a block stay on the same look where each walks all
+// of them: 64-point rows past one block per CU (update pass with 8 looks at
+// 2048 groups 107 us with it and 112 without, at 8192 570 and 585; at 1024, one
+// block per CU, 59 and 54), and 128-point rows whose blocks do not fit on the
+// chip at once, four per CU, which then also run three per CU (mann_lds_pad;
+// 15 looks at 4480 groups 302 us with both and 313 with neither, at 9216 581
+// and 593, one of the two alone no better; at 4096, which fit, 264 and 258).
+// Rows of 32 and 512 points always do (32 points, 16 looks at 1024 groups: 213
+// and 224; 512x512x64 with 8 looks: 1039 us an iteration and 1048); rows of
+// 192 to 384 points run their waves apart.
+bool mann_lockstep(int nx, long groups, int cus) {
+    return (nx == 64 && groups > 4L * cus) || (nx == 128 && groups > 16L * cus);
+}
+// LDS added to a block's 37 KB so that a CU holds three blocks, not four.
+unsigned mann_lds_pad(int nx, bool lockstep) { return nx == 128 && lockstep ? 4096 : 0; }
 
 static int g_col_grid_cap = 0;
 
@@ -541,13 +547,14 @@ hipError_t launch_row(int mode, const RowArgs& a, hipStream_t st) {
 template <int MODE>
 static hipError_t row_update_mann_dispatch(const RowArgs& a, const FuseArgs& f, hipStream_t st) {
     const dim3 grid((unsigned)mann_blocks(a.s, f.split));
+    const unsigned pad = mann_lds_pad(a.s.nx, f.lockstep != 0);
     switch (a.s.nx) {
 #define CASE(N)                                                                          \
     case N:                                                                              \
         if constexpr (MODE == ROW_UPDATE_EXACT)                                          \
             hipLaunchKernelGGL((k_row_upd_mann_exact<N>), grid, dim3(kBlock), 0, st, a, f); \
         else if (f.split == 1)                                                           \
-            hipLaunchKernelGGL((k_row_upd_mann<N, 1>), grid, dim3(kBlock), 0, st, a, f); \
+            hipLaunchKernelGGL((k_row_upd_mann<N, 1>), grid, dim3(kBlock), pad, st, a, f); \
         else if (f.split == 2)                                                           \
             hipLaunchKernelGGL((k_row_upd_mann<N, 2>), grid, dim3(kBlock), 0, st, a, f); \
         else                                                                             \

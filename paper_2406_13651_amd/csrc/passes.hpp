@@ -635,6 +635,8 @@ __device__ __forceinline__ void row_update_mann(const A& a, const F& f, int spli
     }
     __syncthreads();
     uint32_t fb = 0u;
+    // the block's waves stay on the same look, held there by its sum (mann_lockstep)
+    const bool lockstep = split == 1 && (NX == 32 || NX == 512 || (NX <= 128 && f.lockstep));
     // the wave's row buffers, which also take its r_l (rx[k * 64 + lane])
     float* rx = reinterpret_cast<float*>(rb) - (lane / TR) * 2 * RS;
     static_assert(PX * 64 * sizeof(float) <= RPW * RS * sizeof(float2), "a wave's row buffers hold its r_l");
@@ -698,11 +700,15 @@ __device__ __forceinline__ void row_update_mann(const A& a, const F& f, int spli
                     wm1 += om * cabs2(m1);
                 }
             }
-            // the wave's share of the look's sum omega |mu'|^2 (no wait for the
-            // other waves here)
-            const double acc = wave_sums_f64<1>({(double)wm1});
-            if (lane == 0) wsum[l][wave] = acc;
-            if (split == 1 && (NX == 32 || NX == 512 || (NX == 64 && f.lockstep))) __syncthreads();
+            if (lockstep) {
+                const double acc[1] = {wm1};
+                block_sum_store<1>(acc, a.part + (size_t)l * nblk + blk);
+            } else {
+                // the wave's share of the look's sum omega |mu'|^2 (no wait for
+                // the other waves here)
+                const double acc = wave_sums_f64<1>({(double)wm1});
+                if (lane == 0) wsum[l][wave] = acc;
+            }
         }
         if (split > 1) {
             __syncthreads();
@@ -721,7 +727,7 @@ __device__ __forceinline__ void row_update_mann(const A& a, const F& f, int spli
         }
     }
     __syncthreads();
-    if (tid < a.looks) {
+    if (!lockstep && tid < a.looks) {
         // in wave order; of a group's waves only one took this look
         double acc = 0.0;
 #pragma unroll
