@@ -423,7 +423,7 @@ __global__ __launch_bounds__(kBlock) void k_gauss3d(PriorArgs p) {
 // Update pass in us with one, two and four waves, at 256, 512, 768, 1024 and
 // 1536 groups (dashes: not a choice of the rule):
 //   32 points,  4 looks: 22 21 17, 30 37 38, 42 54 60, 60 73 74, 106 118 121
-//   32 points,  8 looks: 45 40 32, 69 59 72, 89 101 111, 116 131 135
+//   32 points,  8 looks: 45 40 32, 69 59 72, 89 101 111, 116 131 135, 219 223 238
 //   64 points,  2 looks: 13 11 -, 14 13 -, 16 18 -, 17 21 -, 29 33 -
 //   64 points,  8 looks: 37 29 19, 44 33 31, 48 50 47, 54 57 67, 94 90 97
 //   128 points, 8 looks: 37 25 17, 40 29 23, 43 36 30, 44 37 39, 62 52 59

@@ -380,12 +380,11 @@ __device__ __forceinline__ void row_fft(float2 (&h)[RowIn<NX>::PX], float2* rb, 
 // so that both report the same sums.  The GPU tests compare a batch, which
 // takes the row pass, with single scenes, which take the slice pass, and fail
 // where a compiler rounds otherwise.
-template <int NX, int TR, bool SLICE = false, int PX, class A>
-__device__ __forceinline__ void row_grad_pointwise(const A& a, float2 (&h)[PX], int t, const float2 (&m)[PX],
+template <bool SLICE, int PX, class A>
+__device__ __forceinline__ void row_grad_pointwise(const A& a, float2 (&h)[PX], const float2 (&m)[PX],
                                                    const float (&rp)[PX], float& dd, float& wd, float& wm) {
 #pragma unroll
     for (int k = 0; k < PX; ++k) {
-        const int x = t + k * TR;
         const float2 ahr = cscale(h[k], a.scale);
         const float om = 1.f / (rp[k] + a.floor_w);
         const float2 d = make_float2(ahr.x * a.inv_s2w - om * m[k].x, ahr.y * a.inv_s2w - om * m[k].y);
@@ -515,7 +514,7 @@ __device__ __forceinline__ void row_item(const A& a, int look, int rgroup, size_
     } else if constexpr (MODE == ROW_GRAD) {
         row_fft_in<NX, +1, true>(in, h, rb, t, L.tw);
         float dd = 0.f, wd = 0.f, wm = 0.f;
-        if (active) row_grad_pointwise<NX, TR>(a, h, t, m, rp, dd, wd, wm);
+        if (active) row_grad_pointwise<false>(a, h, m, rp, dd, wd, wm);
         row_fft<NX, -1, false>(h, rb, t, L.tw);
         if (active)
             for (int b = t; b < s.B; b += TR)
@@ -568,7 +567,8 @@ __device__ __forceinline__ void row_item(const A& a, int look, int rgroup, size_
 // waves exchange their r_l through the row buffers, and each adds those of
 // its share of the voxels in look order -- the same sums, rounding by
 // rounding, as one wave walking every look -- and finishes that share.
-// Partial sums per block: sum omega |mu'|^2 of each look into a.part, the convergence error's (sum_j (r_j - w_bar)^2, N w_bar^2) into f.part.
+// Partial sums per block: sum omega |mu'|^2 of each look into a.part, the
+// convergence error's (sum_j (r_j - w_bar)^2, N w_bar^2) into f.part.
 template <int NX>
 __host__ __device__ constexpr int mann_lds_floats() {
     return 2 * kBlock * RowIn<NX>::PX;
@@ -576,8 +576,7 @@ __host__ __device__ constexpr int mann_lds_floats() {
 
 // LDS: ups[64] holds the agent weights, keep[mann_lds_floats<NX>()] each
 // group's x_bar and w_bar of the previous call ([k][group lane],
-// conflict-free), read back at every look instead of held in registers, and
-// after the looks the waves' sums.
+// conflict-free), read back at every look instead of held in registers.
 template <int NX, int MODE, class A, class F>
 __device__ __forceinline__ void row_update_mann(const A& a, const F& f, int split, int blk, int nblk,
                                                 const RowLds& L, BetaVals bv, float* ups, float* keep) {
@@ -1142,7 +1141,7 @@ __device__ __forceinline__ void slice_grad_item(const A& a, int zl, float2* lds)
         }
         row_fft<NX, +1, true>(h, rb, t, twx);
         float dd = 0.f, wd = 0.f, wm = 0.f;
-        row_grad_pointwise<NX, TR, true>(a, h, t, m, rp, dd, wd, wm);
+        row_grad_pointwise<true>(a, h, m, rp, dd, wd, wm);
         acc[0] += dd;
         acc[1] += wd;
         acc[2] += wm;
